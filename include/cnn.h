@@ -81,8 +81,14 @@ typedef struct cnn_tiles {
 typedef enum cnn_kernel {
   CNN_K_AUTO = 0,     /* let cnn_plan choose                                          */
   CNN_K_DIRECT = 1,   /* one thread per output, fp32 FMA; any shape (correctness path)  */
-  CNN_K_IGEMM = 2,    /* implicit GEMM on MFMA, LDS-staged halo'd In slab + Ker tile,
-                         element-wise staging (any dtype; fallback of CNN_K_IGEMM_PIPE) */
+  CNN_K_IGEMM = 2,    /* implicit GEMM on MFMA, LDS-staged halo'd In slab + Ker tile, any
+                         dtype, stencil and strides, no workspace.  Two kernels:
+                         element-wise staging (tiles are runs of tp outputs), and
+                         two-dimensional tiles (variants from 3000 on: plan.kc
+                         output rows of the flattened (b, w) index by tp/kc
+                         columns; 16-byte loads, double-buffered LDS, fp32 as
+                         three bf16 parts per value; cnn_plan_tiles: tp = the
+                         instantiation's, the model picks the rows)               */
   CNN_K_POINTWISE = 3,/* 1x1 stencils, any stride, bf16, Nc % 8 == 0: the inputs of the
                          tile's outputs gathered (no halo, no unused rows), 64 channels
                          per stage, raw Ker rows as in CNN_K_IGEMM_RAWK              */
@@ -187,7 +193,9 @@ typedef struct cnn_plan_t {
                            take kc = 1 and no workspace only).
                            cnn_plan_tiles picks the smallest kc with no empty
                            slice that gives at least two workgroups per CU,
-                           else ceil(Nc/tc).  0 for the other kernels.        */
+                           else ceil(Nc/tc).  The two-dimensional tiles of
+                           CNN_K_IGEMM: output rows of a tile.  0 for the
+                           other kernels and tilings.                          */
   int64_t tk;           /* output features per workgroup (T_k)                      */
   int64_t tp;           /* outputs of the flattened (b,w,h) index per workgroup     */
   int64_t tc;           /* input features per LDS stage (T_c)                       */

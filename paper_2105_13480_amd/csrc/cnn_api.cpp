@@ -267,6 +267,23 @@ bool cslice_geometry_ok(const VariantC& v, const cnn_plan_t& pl) {
          pl.lds_bytes == cslice_lds_bytes(v, S, Ny) && pl.lds_bytes <= 160 * 1024;
 }
 
+const VariantT* find_variant_t(int id) {
+  int n = 0;
+  const VariantT* vs = variants_tile(&n);
+  for (int i = 0; i < n; ++i)
+    if (vs[i].id == id) return &vs[i];
+  return nullptr;
+}
+
+// Geometry a two-dimensional-tile plan must carry: runs of whole output rows,
+// the workgroups, slab and LDS size they imply.
+bool tile_plan_ok(const VariantT& v, const cnn_plan_t& pl, TileShape* s) {
+  const cnn_problem& p = pl.prob;
+  if (!tile_geometry(v, p, pl.dtype, pl.kc, s) || pl.tp != s->tr * s->ct) return false;
+  const int64_t grid = s->n_rt * s->ncol * ((p.Nk + v.tk - 1) / v.tk);
+  return pl.slab_rows == s->S && pl.grid == grid && pl.lds_bytes == s->lds && pl.ws_bytes == 0;
+}
+
 // Geometry a plain staging plan (and its split form) must carry: the slab,
 // grid and LDS size its tile implies.
 bool igemm_geometry_ok(const Variant& v, const cnn_plan_t& pl) {
@@ -378,6 +395,13 @@ int run_plan(const void* In, const void* Ker, void* Out, const cnn_plan_t& pl, h
       return fail(CNN_E_PLAN, "plan names no matching kernel instantiation (variant %d)", pl.variant);
     if (dry) return CNN_OK;
     e = launch_igemm2(*v2, In, Ker, Out, ws, a, pl.lds_bytes, st);
+  } else if (const VariantT* vt = find_variant_t(pl.variant)) {
+    TileShape ts;
+    if (pl.kernel != CNN_K_IGEMM || vt->dtype != pl.dtype || vt->tk != pl.tk || vt->tc != pl.tc ||
+        !tile_plan_ok(*vt, pl, &ts))
+      return fail(CNN_E_PLAN, "plan names no matching kernel instantiation (variant %d)", pl.variant);
+    if (dry) return CNN_OK;
+    e = launch_tile(*vt, In, Ker, Out, a, ts, pl.grid, st);
   } else {
     const Variant* v = find_variant(pl.variant);
     if (!v || v->kernel != pl.kernel || v->dtype != pl.dtype || v->tk != pl.tk ||

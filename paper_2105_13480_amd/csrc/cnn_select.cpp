@@ -331,6 +331,98 @@ static bool eval_srows(const cnn_problem& p, int dtype, const VariantQ& v, const
   return true;
 }
 
+// What the two-dimensional-tile kernel's work costs on one CU, in
+// microseconds, fitted (least squares on log time) to some 6000 launches of
+// its instantiations on layers of every kind it takes, timed on one MI355X.
+// A workgroup's stage takes the longer of its matrix and LDS work, plus its
+// loads, times the workgroups that share the CU, and at least a latency.
+struct TileCost {
+  double mfma, lds;     // per microsecond of matrix / LDS work at 2 GHz
+  double vmem;          // per microsecond of load issue at 16 clocks a wave's load
+  double stage_us;      // a stage's least time
+  double wg_us;         // per workgroup: set-up, the first stage's latency
+  double out_us;        // per kilobyte of Out
+  double fixed_us;      // per launch
+  double first_vmem;    // the first stage's loads, which nothing hides
+};
+static const TileCost& tile_cost(const VariantT& v) {
+  static const TileCost f32 = {0.934, 2.161, 0.0, 1.96, 2.986, 0.006, 1.865, 0.0};
+  static const TileCost k3 = {1.072, 0.74, 1.942, 1.23, 4.026, 0.025, 1.385, 0.28};
+  static const TileCost k1 = {1.2, 1.413, 3.39, 1.498, 5.591, 0.0, 0.451, 4.24};
+  static const TileCost any = {1.2, 1.8, 1.328, 2.313, 5.118, 0.018, 0.04, 5.662};
+  return v.dtype == CNN_F32 ? f32 : v.nr == 3 ? k3 : v.nr == 1 ? k1 : any;
+}
+
+// The kernel's own time (no HBM bound) with the geometry s.
+static double tile_us(const cnn_problem& p, int dtype, const VariantT& v, const TileShape& s,
+                      const cnn_budget& bud) {
+  const TileCost& c = tile_cost(v);
+  const double es = in_bytes(dtype), RS = (double)(p.Nr * p.Ns);
+  const bool f32 = dtype == CNN_F32;
+  const double planes = f32 ? 3 : 1, ker_vecs = f32 ? 2 : 1, products = f32 ? 6 : 1;
+  const double waves = (double)v.waves, ks = (double)(v.tc / 16), groups = (double)(v.tc / 8);
+  const double mb = (double)v.acc / 16 / (double)v.nb, nb = (double)v.nb;
+  const double items = (double)s.S * (double)ceil_div(s.cw, s.pw);
+  const double clk = 2000.0;  // per microsecond
+  const double mfma = waves / 4 * RS * ks * mb * nb * products * 32 / clk;
+  const double lds = (waves * RS * ks * (mb * ker_vecs + nb * planes) * 8 +
+                      (double)s.SP * groups * planes / 4 + (double)(v.tk * v.tc) * RS * es / 64) / clk;
+  const double ker_loads = v.nr == 3 ? 3.0 * (double)(v.tk * v.tc) / (f32 ? 1 : 2)
+                                     : (double)(v.tk * s.nch) * (v.nr == 1 || f32 ? 1 : 2);
+  const double vmem = (items * groups * 8 * (s.gather ? 2 : 1) + ker_loads) / 64 * 16 / clk;
+  const double out_kb = (double)(v.tk * s.tr * s.ct) * out_bytes(dtype) / 1000;
+  const int64_t occ = std::max<int64_t>(1, std::min<int64_t>(v.occ, bud.lds_bytes / s.lds));
+  const int64_t n = ceil_div(s.n_rt * s.ncol * ceil_div(p.Nk, v.tk), bud.cus);  // per CU
+  const double stages = (double)ceil_div(p.Nc, v.tc);
+  auto round = [&](double k) {  // k workgroups at once
+    const double st = std::max(k * (std::max(c.mfma * mfma, c.lds * lds) + c.vmem * vmem), c.stage_us);
+    return c.wg_us + k * (c.first_vmem * vmem + c.out_us * out_kb) + stages * st;
+  };
+  return c.fixed_us + (double)(n / occ) * round((double)occ) +
+         (n % occ ? round((double)(n % occ)) : 0.0);
+}
+
+// Two-dimensional-tile kernel (conv_tile) with runs of tr output rows: 0 for
+// the model's best.
+static bool eval_tile(const cnn_problem& p, int dtype, const VariantT& v, int64_t tr,
+                      const cnn_budget& bud, cnn_plan_t* plan) {
+  TileShape s;
+  if (tr == 0) {
+    double best = 0.0;
+    TileShape c;
+    for (int64_t r = 1; r <= std::min<int64_t>(v.tp, p.Nb * p.Nw); ++r) {
+      if (!tile_geometry(v, p, dtype, r, &c) || c.lds > bud.lds_bytes) continue;
+      const double t = tile_us(p, dtype, v, c, bud);
+      if (tr == 0 || t < best) {
+        best = t;
+        tr = r;
+        s = c;
+      }
+    }
+    if (tr == 0) return false;
+  } else if (!tile_geometry(v, p, dtype, tr, &s)) {
+    return false;
+  }
+  // (priced by Eq. (1) as runs of as many outputs: an upper bound of its In
+  // term where the runs are cut into bands)
+  if (!eval_tiling(p, dtype, v.id, v.tk, tr * s.ct, v.tc, v.acc, s.S, s.lds, 0, bud, plan))
+    return false;
+  plan->kc = (int32_t)tr;
+  plan->grid = s.n_rt * s.ncol * ceil_div(p.Nk, v.tk);
+  if (plan->grid > 0x7fffffffLL) return false;
+  plan->mfma_flops = 2.0 * v.tk * v.tp * (double)(ceil_div(p.Nc, v.tc) * v.tc * p.Nr * p.Ns) *
+                     (double)plan->grid * (dtype == CNN_F32 ? 6 : 1);
+  return true;
+}
+
+static const VariantT* tile_variant(int kernel, int id) {
+  int n = 0;
+  const VariantT* vt = variants_tile(&n);
+  for (int i = 0; kernel == CNN_K_IGEMM && i < n; ++i)
+    if (vt[i].id == id) return &vt[i];
+  return nullptr;
+}
+
 // The XCD / L2 level the two-level model (Eq. (3) one level up) sees: 8 XCDs
 // of one 4 MiB L2 each on MI355X.
 static const int64_t kXcds = 8;
@@ -442,6 +534,12 @@ static double model_us(const cnn_plan_t& pl, const cnn_budget& bud, double w_out
     // 64 lanes x 4 SIMDs x one fp32 FMA (2 flops) per clock per CU
     const double t = pl.flops / (cus * 512.0 * clk_per_us * fc.mfma_eff);
     return std::max(t, pl.hbm_bytes / (hbm_gbs(w_out) * 1e3)) + kLaunchUs;
+  }
+  if (const VariantT* v = tile_variant(pl.kernel, pl.variant)) {
+    TileShape s;
+    const double t = tile_geometry(*v, p, pl.dtype, pl.kc, &s)
+                         ? tile_us(p, pl.dtype, *v, s, bud) : 0.0;
+    return std::max(t, pl.hbm_bytes / (hbm_gbs(w_out) * 1e3) + kLaunchUs);
   }
   const double kc = pl.kernel == CNN_K_SPLITC ? (double)pl.kc : 1.0;
   const double wgs = (double)pl.grid * kc;
@@ -724,6 +822,12 @@ int enumerate_plans(const cnn_problem& p, int dtype, const cnn_budget& bud, cnn_
         add(cand, CNN_K_SPLITC);
       }
     }
+  int ntl = 0;
+  const VariantT* vtl = variants_tile(&ntl);
+  for (int i = 0; i < ntl; ++i) {
+    if (vtl[i].dtype != dtype) continue;
+    if (eval_tile(p, dtype, vtl[i], 0, bud, &cand)) add(cand, CNN_K_IGEMM);
+  }
   int ncs = 0;
   const VariantC* vcs = variants_cslice(&ncs);
   for (int i = 0; i < ncs; ++i)
@@ -933,6 +1037,9 @@ int list_variants(cnn_variant_t* out, int cap) {
   const VariantQ* vq = variants_srows(&c);
   for (int i = 0; i < c; ++i)
     add(CNN_K_SROWS, vq[i].id, vq[i].dtype, vq[i].nr, vq[i].ns, vq[i].L, vq[i].tk, 0, 16);
+  const VariantT* vt = variants_tile(&c);
+  for (int i = 0; i < c; ++i)
+    add(CNN_K_IGEMM, vt[i].id, vt[i].dtype, vt[i].nr, vt[i].ns, 0, vt[i].tk, vt[i].tp, vt[i].tc);
   const VariantC* vc = variants_cslice(&c);
   for (int i = 0; i < c; ++i)
     add(CNN_K_SPLITC, vc[i].id, vc[i].dtype, vc[i].nr, vc[i].ns, vc[i].mode, vc[i].tk, vc[i].tp,

@@ -174,6 +174,37 @@ bool srows_fits(const VariantQ& v, const cnn_problem& p);
 hipError_t launch_srows(const VariantQ& v, const void* In, const void* Ker, void* Out, void* ws,
                         const ConvArgs& a, int64_t lds_bytes, hipStream_t stream);
 
+// A two-dimensional-tile instantiation (conv_tile; a CNN_K_IGEMM member): tk
+// features x up to tp outputs, tc channels per stage, any stencil and
+// strides unless nr x ns fix the stencil, no workspace.
+struct VariantT {
+  int32_t id;
+  int32_t dtype;
+  int32_t tk, tp, tc;  // tp = outputs the accumulators hold
+  int32_t acc;
+  int32_t nr, ns;      // compile-time stencil (0 = any)
+  int32_t maxp, kch;   // In items and (but for 3x3) Ker items per thread and stage
+  int32_t occ;         // workgroups per CU its registers allow
+  int32_t nb;          // blocks of 32 outputs per wave
+  int32_t waves;
+};
+const VariantT* variants_tile(int* count);
+// Its tile on a problem: runs of tr whole output rows, cut into ncol bands
+// of ct columns.
+struct TileShape {
+  int64_t tr, ct, ncol;  // output rows, columns per band, bands
+  int64_t n_rt;          // runs of rows
+  int64_t cw, hp, pitch; // staged columns, LDS columns per residue of the h stride, row pitch
+  int64_t S, SP;         // staged rows at most, LDS vectors per channel group
+  int64_t nch, njt;      // Ker items per feature and stage, runs of taps per channel
+  int64_t lds;           // bytes
+  int64_t pw;            // columns of a staging item
+  int32_t squeeze, gather, form;
+};
+bool tile_geometry(const VariantT& v, const cnn_problem& p, int dtype, int64_t tr, TileShape* s);
+hipError_t launch_tile(const VariantT& v, const void* In, const void* Ker, void* Out,
+                       const ConvArgs& a, const TileShape& s, int64_t grid, hipStream_t stream);
+
 // Ker repack for the pipelined kernels (defined with conv_igemm2).
 __global__ void pack_ker_bf16(const uint16_t* __restrict__ Ker, uint32_t __attribute__((ext_vector_type(4)))* __restrict__ P,
                               ConvArgs a, int TK, int TC, int blk_vecs, int64_t total_vecs);

@@ -1,0 +1,122 @@
+"""The two-dimensional-tile kernel (CNN_K_IGEMM, variants from 3000 on): every
+form of its staging, at the edges of its tiles, against the fp64 oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2105_13480_amd import cnn, inputs
+
+from gpu_helpers import TOL, errors, run, say
+
+pytestmark = pytest.mark.gpu
+
+MODES = {"f32": cnn.CNN_F32, "bf16": cnn.CNN_BF16, "bf16_obf16": cnn.CNN_BF16_OBF16}
+
+# (Nb, Nc, Nk, Nw, Nh, Nr, Ns, sw, sh)
+SHAPES = [
+    (2, 17, 33, 20, 75, 3, 3, 1, 1),    # column bands, one channel in the last stage
+    (3, 16, 64, 7, 7, 3, 3, 1, 1),      # tiles across images, whole channels
+    (1, 5, 3, 6, 300, 3, 3, 1, 1),      # rows wider than a tile, fewer channels than a stage
+    (2, 33, 70, 9, 14, 3, 3, 2, 2),     # columns by parity
+    (2, 24, 40, 5, 9, 3, 3, 3, 3),      # stride 3: position pairs
+    (1, 31, 45, 4, 2, 3, 3, 1, 1),      # four columns: pairs
+    (2, 65, 66, 11, 13, 1, 1, 1, 1),    # 1x1, odd rows, odd Ker elements
+    (3, 79, 131, 9, 17, 1, 1, 2, 2),    # 1x1 gathered at stride 2
+    (2, 72, 40, 6, 10, 1, 1, 2, 3),     # 1x1 gathered at stride 3, rows squeezed
+    (2, 19, 21, 9, 11, 1, 7, 1, 1),     # runtime stencils: 7 taps, odd
+    (2, 21, 37, 9, 11, 7, 1, 2, 2),     # 1 wide, gathered, 7 rows
+    (2, 18, 35, 10, 12, 3, 2, 2, 1),    # 6 taps
+    (1, 23, 50, 12, 21, 5, 5, 1, 1),    # 25 taps
+    (2, 16, 20, 8, 9, 4, 4, 2, 2),      # 16 taps, even stencil at stride 2
+    (1, 9, 34, 8, 10, 7, 7, 2, 2),      # 49 taps
+    (2, 20, 24, 6, 15, 2, 3, 3, 1),     # rows between reads not staged
+    (1, 1, 1, 1, 2, 1, 1, 1, 1),        # the smallest
+    (1, 3, 1, 1, 8, 1, 1, 1, 1),        # one row of one vector, three Ker elements
+]
+
+
+def _ints(dims, mode, seed):
+    return inputs.make_arrays(*dims, "f32" if mode == "f32" else "bf16", seed_in=seed,
+                              seed_ker=seed + 1, in_dist=("int", -2, 2), ker_dist=("int", -2, 2))
+
+
+def _tile_plans(dims, mode):
+    """The tile plans of a problem for a full and for a small GPU budget (few
+    CUs: the largest tiles)."""
+    seen, out = set(), []
+    for cus in (256, 2):
+        for c in cnn.plan_candidates(cnn.problem(*dims), MODES[mode], cnn.budget(cus=cus)):
+            if c.kernel == cnn.K_IGEMM and c.variant >= 3000 and (c.variant, c.kc) not in seen:
+                seen.add((c.variant, c.kc))
+                out.append(c)
+    return out
+
+
+@pytest.mark.parametrize("mode", list(MODES))
+@pytest.mark.parametrize("dims", SHAPES, ids=str)
+def test_tile_exact_integers(dims, mode):
+    """Integer inputs: every sum exact in fp32, so bit-exact in fp32 Out and
+    its rounding in bf16 Out."""
+    In, Ker = _ints(dims, mode, seed=sum(dims))
+    want = oracle.conv(In, Ker, dims[7], dims[8])
+    if mode == "bf16_obf16":
+        want = oracle.widen(inputs.f32_to_bf16_bits(want.astype(np.float32)))
+    plans = _tile_plans(dims, mode)
+    assert plans or max(dims[5], dims[6]) > 5
+    for pl in plans:
+        say(f"[tile] dims={dims} mode={mode} v{pl.variant} rows={pl.kc} tp={pl.tp} grid={pl.grid}")
+        got = run(In, Ker, dims[7], dims[8], mode, plan=pl)
+        assert np.array_equal(got, want), (pl.variant, pl.kc)
+
+
+@pytest.mark.parametrize("dims", [(2, 70, 70, 13, 21, 3, 3, 1, 1), (2, 130, 40, 9, 11, 1, 1, 2, 2),
+                                  (1, 40, 33, 12, 12, 5, 5, 1, 1)], ids=str)
+def test_tile_f32_split_error(dims):
+    """fp32 as three bf16 parts.  Per product the parts that are dropped come
+    to at most 2^-7 2^-16 twice, less than 4 units of 2^-24; an accumulation of
+    six 16-channel products per tap and channel stage rounds 6 K / 16 times,
+    K = Nc Nr Ns padded to whole stages of 32 channels."""
+    Nc, RS = dims[1], dims[5] * dims[6]
+    bound = (6 * -(-Nc // 32) * 2 * RS + 4) * 2.0 ** -24
+    In, Ker = inputs.make_arrays(*dims, "f32", seed_in=5, seed_ker=6,
+                                 in_dist=("uniform", -1.0, 1.0), ker_dist=("he",))
+    want, absv = oracle.conv(In, Ker, dims[7], dims[8], with_abs=True)
+    for pl in _tile_plans(dims, "f32"):
+        say(f"[tile] f32 error dims={dims} v{pl.variant} rows={pl.kc}")
+        nw, cond, _ = errors(run(In, Ker, dims[7], dims[8], "f32", plan=pl), want, absv)
+        assert cond <= min(bound, TOL["f32"]) and nw <= TOL["f32"], (pl.variant, nw, cond)
+
+
+@pytest.mark.parametrize("dims", [(2, 20, 40, 9, 13, 3, 3, 1, 1), (1, 33, 34, 6, 9, 1, 1, 2, 2),
+                                  (1, 18, 20, 8, 9, 4, 2, 1, 2)], ids=str)
+@pytest.mark.parametrize("case", ["inf", "nan", "lowest", "tiny", "subnormal"])
+def test_tile_f32_outside_the_split(dims, case):
+    """Values that three bf16 parts do not hold: infinities and NaN reach
+    exactly the outputs that the direct fp32 kernel's reach, the type's lowest
+    value stays finite, and inputs near the bottom of the range keep fp32's
+    relative accuracy."""
+    In, Ker = inputs.make_arrays(*dims, "f32", seed_in=8, seed_ker=9,
+                                 in_dist=("uniform", 0.25, 1.0), ker_dist=("he",))
+    In = In.copy()
+    if case == "inf":
+        In[0, 3, 2, 4], In[-1, 5, 1, 1] = np.inf, -np.inf
+    elif case == "nan":
+        In[0, 3, 2, 4] = np.nan
+    elif case == "lowest":
+        In[0, 3, 2, 4] = np.finfo(np.float32).min
+    elif case == "tiny":
+        In *= np.float32(1e-34)
+    else:
+        In[0, 3] *= np.float32(1e-40)
+    prob = cnn.problem(*dims)
+    say(f"[tile] f32 {case} dims={dims}: direct kernel")
+    ref = run(In, Ker, dims[7], dims[8], "f32", plan=cnn.plan_tiles(prob, cnn.CNN_F32, cnn.K_DIRECT))
+    scale = np.abs(ref[np.isfinite(ref)]).max()
+    for pl in _tile_plans(dims, "f32"):
+        say(f"[tile] f32 {case} dims={dims} v{pl.variant} rows={pl.kc}")
+        got = run(In, Ker, dims[7], dims[8], "f32", plan=pl)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), pl.variant
+        assert np.array_equal(np.isinf(got), np.isinf(ref)), pl.variant
+        fine = np.isfinite(ref)
+        assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+        assert np.abs(got[fine] - ref[fine]).max() <= 1e-5 * scale, pl.variant
