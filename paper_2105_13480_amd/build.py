@@ -22,7 +22,7 @@ LIB = os.path.join(PKG, "libcnn_mi355x.so")
 
 SOURCES = ["cnn_api.cpp", "cnn_select.cpp", "k_direct.hip", "k_igemm.hip", "k_igemm2.hip",
            "k_igemm3.hip", "k_igemm4.hip", "k_smallc.hip", "k_rows.hip", "k_gemm1.hip",
-           "k_srows.hip", "k_cslice.hip", "k_tile.hip", "k_tile_f32.hip",
+           "k_srows.hip", "k_cslice.hip", "k_small.hip", "k_tile.hip", "k_tile_f32.hip",
            "k_tile_3x3_bf16.hip", "k_tile_3x3_obf16.hip", "k_tile_any_bf16.hip",
            "k_tile_any_obf16.hip", "cnn_static.hip"]
 

@@ -284,6 +284,20 @@ bool tile_plan_ok(const VariantT& v, const cnn_plan_t& pl, TileShape* s) {
   return pl.slab_rows == s->S && pl.grid == grid && pl.lds_bytes == s->lds && pl.ws_bytes == 0;
 }
 
+const VariantM* find_variant_m(int id) {
+  int n = 0;
+  const VariantM* vs = variants_small(&n);
+  for (int i = 0; i < n; ++i)
+    if (vs[i].id == id) return &vs[i];
+  return nullptr;
+}
+
+// Geometry a few-outputs plan must carry.
+bool small_plan_ok(const VariantM& v, const cnn_plan_t& pl, SmallShape* s) {
+  return small_geometry(v, pl.prob, pl.dtype, s) && pl.slab_rows == s->S && pl.grid == s->grid &&
+         pl.lds_bytes == s->lds && pl.ws_bytes == 0 && pl.tc == pl.prob.Nc;
+}
+
 // Geometry a plain staging plan (and its split form) must carry: the slab,
 // grid and LDS size its tile implies.
 bool igemm_geometry_ok(const Variant& v, const cnn_plan_t& pl) {
@@ -367,7 +381,13 @@ int run_plan(const void* In, const void* Ker, void* Out, const cnn_plan_t& pl, h
                   "(0 for the atomic-sum and direct instantiations; kc = 1 for the direct ones)",
                   (long long)stages);
     if (dry) return CNN_OK;
-    e = vc ? launch_cslice(*vc, In, Ker, Out, ws, a, pl.lds_bytes, pl.kc, pl.dtype, st)
+    // the direct form on the few-outputs kernel, where that fits: its waves
+    // share the channels, 128 workgroups instead of 16 on the batch-1 deep
+    // layer (SMALL_LATE_FIGURES)
+    SmallShape ms;
+    const VariantM* vm = vc && vc->mode == 2 ? small_direct(p, pl.dtype, &ms) : nullptr;
+    e = vm ? launch_small(*vm, In, Ker, Out, a, ms, st)
+        : vc ? launch_cslice(*vc, In, Ker, Out, ws, a, pl.lds_bytes, pl.kc, pl.dtype, st)
            : launch_splitc(*v, In, Ker, Out, ws, a, pl.lds_bytes, pl.kc, pl.dtype, st);
   } else if (pl.kernel == CNN_K_SMALLC) {
     const VariantS* vs = find_variant_s(pl.variant);
@@ -395,6 +415,13 @@ int run_plan(const void* In, const void* Ker, void* Out, const cnn_plan_t& pl, h
       return fail(CNN_E_PLAN, "plan names no matching kernel instantiation (variant %d)", pl.variant);
     if (dry) return CNN_OK;
     e = launch_igemm2(*v2, In, Ker, Out, ws, a, pl.lds_bytes, st);
+  } else if (const VariantM* vm = find_variant_m(pl.variant)) {
+    SmallShape ms;
+    if (pl.kernel != CNN_K_IGEMM || vm->dtype != pl.dtype || vm->tk != pl.tk || vm->tp != pl.tp ||
+        !small_plan_ok(*vm, pl, &ms))
+      return fail(CNN_E_PLAN, "plan names no matching kernel instantiation (variant %d)", pl.variant);
+    if (dry) return CNN_OK;
+    e = launch_small(*vm, In, Ker, Out, a, ms, st);
   } else if (const VariantT* vt = find_variant_t(pl.variant)) {
     TileShape ts;
     if (pl.kernel != CNN_K_IGEMM || vt->dtype != pl.dtype || vt->tk != pl.tk || vt->tc != pl.tc ||

@@ -332,7 +332,7 @@ static bool eval_srows(const cnn_problem& p, int dtype, const VariantQ& v, const
 }
 
 // What the two-dimensional-tile kernel's work costs on one CU, in
-// microseconds, fitted (least squares on log time) to some 6000 launches of
+// microseconds, fitted (least squares on log time) to some 11000 launches of
 // its instantiations on layers of every kind it takes, timed on one MI355X.
 // A workgroup's stage takes the longer of its matrix and LDS work, plus its
 // loads, times the workgroups that share the CU, and at least a latency.
@@ -346,10 +346,10 @@ struct TileCost {
   double first_vmem;    // the first stage's loads, which nothing hides
 };
 static const TileCost& tile_cost(const VariantT& v) {
-  static const TileCost f32 = {0.934, 2.161, 0.0, 1.96, 2.986, 0.006, 1.865, 0.0};
-  static const TileCost k3 = {1.072, 0.74, 1.942, 1.23, 4.026, 0.025, 1.385, 0.28};
-  static const TileCost k1 = {1.2, 1.413, 3.39, 1.498, 5.591, 0.0, 0.451, 4.24};
-  static const TileCost any = {1.2, 1.8, 1.328, 2.313, 5.118, 0.018, 0.04, 5.662};
+  static const TileCost f32 = {0.981, 2.104, 0.0, 2.027, 3.536, 0.001, 1.706, 0.0};
+  static const TileCost k3 = {1.127, 0.754, 1.445, 0.849, 4.05, 0.021, 1.877, 0.003};
+  static const TileCost k1 = {1.06, 0.402, 3.162, 1.461, 4.415, 0.0, 0.0, 6.471};
+  static const TileCost any = {1.2, 2.415, 0.0, 1.819, 5.597, 0.009, 0.0, 3.602};
   return v.dtype == CNN_F32 ? f32 : v.nr == 3 ? k3 : v.nr == 1 ? k1 : any;
 }
 
@@ -392,6 +392,9 @@ static bool eval_tile(const cnn_problem& p, int dtype, const VariantT& v, int64_
     TileShape c;
     for (int64_t r = 1; r <= std::min<int64_t>(v.tp, p.Nb * p.Nw); ++r) {
       if (!tile_geometry(v, p, dtype, r, &c) || c.lds > bud.lds_bytes) continue;
+      // narrow bands store and load short pieces of rows: 64 -> 64 features at
+      // 224x224, batch 8, in bands of 32 columns 40 us, of 18 columns 51
+      if (c.ncol > 1 && c.ct < 32) continue;
       const double t = tile_us(p, dtype, v, c, bud);
       if (tr == 0 || t < best) {
         best = t;
@@ -423,6 +426,62 @@ static const VariantT* tile_variant(int kernel, int id) {
   return nullptr;
 }
 
+// Few-outputs kernel (conv_small).
+static bool eval_small(const cnn_problem& p, int dtype, const VariantM& v, const cnn_budget& bud,
+                       cnn_plan_t* plan) {
+  SmallShape s;
+  // few outputs: up to four workgroups per CU (with 20 per CU a 3-channel
+  // 3x3 stride-2 layer ran 30 us against 19 on the few-channel kernel)
+  if (!small_geometry(v, p, dtype, &s) || s.grid > 4 * bud.cus) return false;
+  if (!eval_tiling(p, dtype, v.id, v.tk, v.tp, p.Nc, v.acc, s.S, s.lds, 0, bud, plan)) return false;
+  plan->grid = s.grid;
+  const double ks = dtype == CNN_F32 ? 16 : 32;
+  plan->mfma_flops = 2.0 * 16 * v.tp * std::ceil((double)(p.Nc * p.Nr * p.Ns) / ks) * ks *
+                     (double)s.grid;
+  return true;
+}
+
+static const VariantM* small_variant(int kernel, int id) {
+  int n = 0;
+  const VariantM* vm = variants_small(&n);
+  for (int i = 0; kernel == CNN_K_IGEMM && i < n; ++i)
+    if (vm[i].id == id) return &vm[i];
+  return nullptr;
+}
+
+// Its time: rounds of as many workgroups as LDS and 2048 threads per CU allow,
+// each a latency, its Ker and In bytes at what a CU keeps outstanding, and its
+// gathers (wave reads); fitted like the tile kernel's, to 567 launches.
+static double small_us(const cnn_problem& p, int dtype, const VariantM& v, const SmallShape& s,
+                       const cnn_budget& bud) {
+  const double es = in_bytes(dtype), K = (double)(p.Nc * p.Nr * p.Ns);
+  const double ker_kb = (double)v.tk * K * es / 1000, in_kb = (double)(p.Nc * s.LP) * es / 1000;
+  const double gathers = std::ceil(K / (dtype == CNN_F32 ? 16 : 32)) * (double)(v.tp / 16) *
+                         (dtype == CNN_F32 ? 4 : 8);
+  const int64_t occ = std::max<int64_t>(1, std::min<int64_t>(bud.lds_bytes / s.lds, 32 / s.waves));
+  const int64_t n = ceil_div(s.grid, bud.cus);
+  auto round = [&](double k) {
+    return 2.37 + (double)(ceil_div(p.Nc, s.chk) - 1) * 0.12 +
+           k * (in_kb * 0.0314 + ker_kb * 0.0104 + gathers * 0.0022);
+  };
+  return 2.04 + (double)(n / occ) * round((double)occ) + (n % occ ? round((double)(n % occ)) : 0.0);
+}
+
+const VariantM* small_direct(const cnn_problem& p, int dtype, SmallShape* s) {
+  const cnn_budget bud = {256, 160 * 1024, 128, 2};
+  const VariantM* best = nullptr;
+  double tb = 0.0;
+  int n = 0;
+  const VariantM* vm = variants_small(&n);
+  for (int i = 0; i < n; ++i) {
+    SmallShape c;
+    if (vm[i].dtype != dtype || !small_geometry(vm[i], p, dtype, &c)) continue;
+    const double t = small_us(p, dtype, vm[i], c, bud);
+    if (!best || t < tb) best = &vm[i], tb = t, *s = c;
+  }
+  return best;
+}
+
 // The XCD / L2 level the two-level model (Eq. (3) one level up) sees: 8 XCDs
 // of one 4 MiB L2 each on MI355X.
 static const int64_t kXcds = 8;
@@ -448,8 +507,10 @@ static const double kSrowsWriteRate = 1.18;
 static double mfma_rate(int dtype) { return dtype == CNN_F32 ? 256.0 : 4096.0; }
 
 // What each kernel family's implementation adds to the work and the bytes,
-// fitted (least squares on log time) to every candidate of the seven
-// benchmark workloads timed on one MI355X: the fraction of the sustained
+// fitted (least squares on log time) to candidates of the seven benchmark
+// workloads and of 240 other layers (of every size, type and stencil) timed
+// on one MI355X; the row, ring, stride-2 band and channel-slice kernels' to
+// the workloads alone: the fraction of the sustained
 // MFMA rate its inner loop reaches; a fixed cost per workgroup (set-up,
 // the resident Ker tile); and the time of one channel stage when it is not
 // MFMA-bound: a latency plus the stage's share of the Eq. (1) traffic at a
@@ -461,9 +522,9 @@ struct FamilyCost {
   double stage_gbs;     // per stage, Eq. (1) bytes per CU per second (GB/s)
 };
 
-static FamilyCost family_cost(int kernel, int variant) {
+static FamilyCost family_cost(int kernel, int variant, int dtype) {
   switch (kernel) {
-    case CNN_K_ROWS: return {0.73, 6.37, 0.01, 58.0};
+    case CNN_K_ROWS: return {0.73, 5.30, 0.01, 58.0};
     case CNN_K_SROWS: {
       int n = 0;
       const VariantQ* vq = variants_srows(&n);
@@ -478,21 +539,21 @@ static FamilyCost family_cost(int kernel, int variant) {
       int n = 0;
       const VariantG* vg = variants_gemm1(&n);
       for (int i = 0; i < n; ++i)
-        if (vg[i].id == variant && vg[i].s2 == 2) return {0.99, 1.22, 0.40, 50.0};  // DMA ring
-      return {0.36, 1.28, 0.56, 50.1};
+        if (vg[i].id == variant && vg[i].s2 == 2) return {0.99, 3.72, 0.52, 84.4};  // DMA ring
+      return {0.51, 3.75, 0.79, 33.1};
     }
     case CNN_K_SMALLC: {
       int n = 0;
       const VariantS* vs = variants_smallc(&n);
       for (int i = 0; i < n; ++i)
-        if (vs[i].id == variant && vs[i].nc) return {0.17, 1.52, 0.17, 49.7};  // stencil compiled in
-      return {0.17, 1.66, 0.17, 49.7};
+        if (vs[i].id == variant && vs[i].nc) return {0.73, 6.81, 0.18, 53.2};  // stencil compiled in
+      return {0.28, 6.53, 0.0, 1000.0};
     }
-    case CNN_K_IGEMM_RAWK: return {0.49, 1.67, 2.41, 29.5};
-    case CNN_K_POINTWISE: return {0.98, 37.19, 0.41, 100.0};
-    case CNN_K_IGEMM_PIPE: return {0.74, 3.80, 2.51, 30.2};
-    case CNN_K_IGEMM_DMA: return {0.55, 6.62, 0.93, 34.8};
-    case CNN_K_IGEMM_WIDE: return {1.00, 0.00, 7.53, 100.0};
+    case CNN_K_IGEMM_RAWK: return {0.49, 3.13, 3.74, 90.7};
+    case CNN_K_POINTWISE: return {0.98, 4.28, 2.84, 16.6};
+    case CNN_K_IGEMM_PIPE: return {0.74, 6.21, 3.63, 95.0};
+    case CNN_K_IGEMM_DMA: return {0.43, 6.47, 0.93, 30.1};
+    case CNN_K_IGEMM_WIDE: return {1.00, 4.96, 5.02, 34.8};
     case CNN_K_SPLITC: {
       int n = 0;
       const VariantC* vc = variants_cslice(&n);
@@ -502,9 +563,10 @@ static FamilyCost family_cost(int kernel, int variant) {
       for (int i = 0; i < n; ++i)
         if (vc[i].id == variant)
           return {0.50, vc[i].mode == 1 ? 2.30 : 1.00, vc[i].mode == 2 ? 2.90 : 1.50, 50.0};
-      return {0.51, 3.07, 1.65, 4.1};
+      return dtype == CNN_F32 ? FamilyCost{0.373, 2.78, 0.0, 4.4} : FamilyCost{0.13, 4.65, 1.49, 3.55};
     }
-    case CNN_K_IGEMM: return {0.40, 0.00, 2.14, 3.4};
+    case CNN_K_IGEMM:
+      return dtype == CNN_F32 ? FamilyCost{0.343, 1.46, 0.81, 5.66} : FamilyCost{0.137, 0.0, 8.87, 4.77};
     default: return {0.25, 0.0, 0.0, 1.0};  // direct: fp32 vector FMAs
   }
 }
@@ -526,7 +588,7 @@ static double hbm_gbs(double w) {
 // plan adds its launch.
 static double model_us(const cnn_plan_t& pl, const cnn_budget& bud, double w_out) {
   const cnn_problem& p = pl.prob;
-  const FamilyCost fc = family_cost(pl.kernel, pl.variant);
+  const FamilyCost fc = family_cost(pl.kernel, pl.variant, pl.dtype);
   const double clk_per_us = kClkGHz * 1e3;
   const double cus = (double)bud.cus;
   const double n_out = (double)(p.Nb * p.Nk * p.Nw * p.Nh);
@@ -540,6 +602,23 @@ static double model_us(const cnn_plan_t& pl, const cnn_budget& bud, double w_out
     const double t = tile_geometry(*v, p, pl.dtype, pl.kc, &s)
                          ? tile_us(p, pl.dtype, *v, s, bud) : 0.0;
     return std::max(t, pl.hbm_bytes / (hbm_gbs(w_out) * 1e3) + kLaunchUs);
+  }
+  if (const VariantM* v = small_variant(pl.kernel, pl.variant)) {
+    SmallShape s;
+    const double t = small_geometry(*v, p, pl.dtype, &s) ? small_us(p, pl.dtype, *v, s, bud) : 0.0;
+    return std::max(t, pl.hbm_bytes / (hbm_gbs(w_out) * 1e3) + kLaunchUs);
+  }
+  if (pl.kernel == CNN_K_SPLITC && pl.kc == 1 && pl.ws_bytes == 0) {
+    int n = 0;
+    const VariantC* vc = variants_cslice(&n);
+    for (int i = 0; i < n; ++i) {
+      SmallShape s;
+      const VariantM* v = vc[i].id == pl.variant && vc[i].mode == 2
+                              ? small_direct(p, pl.dtype, &s) : nullptr;
+      if (v)
+        return std::max(small_us(p, pl.dtype, *v, s, bud),
+                        pl.hbm_bytes / (hbm_gbs(w_out) * 1e3) + kLaunchUs);
+    }
   }
   const double kc = pl.kernel == CNN_K_SPLITC ? (double)pl.kc : 1.0;
   const double wgs = (double)pl.grid * kc;
@@ -590,7 +669,10 @@ static void fill_common(const cnn_problem& p, int dtype, const cnn_budget& bud,
     plan->hbm_bytes = t[0] + t[1] + t[2];
     w_out = plan->hbm_bytes > 0.0 ? t[0] / plan->hbm_bytes : 0.0;
   }
-  plan->model_us = model_us(*plan, bud, w_out);
+  // On a grid of 2.1 %: plans the 2 % rule takes for equal then are equal, so
+  // that its order is one (a near tie of near ties otherwise has no first).
+  const double step = std::log(1.021);
+  plan->model_us = std::exp(std::ceil(std::log(model_us(*plan, bud, w_out)) / step - 1e-9) * step);
 }
 
 void direct_plan(const cnn_problem& p, int dtype, const cnn_budget& bud, cnn_plan_t* plan) {
@@ -830,10 +912,17 @@ int enumerate_plans(const cnn_problem& p, int dtype, const cnn_budget& bud, cnn_
   }
   int ncs = 0;
   const VariantC* vcs = variants_cslice(&ncs);
+  bool direct = false;  // the direct channel-slice plan stands for the few-outputs kernel
   for (int i = 0; i < ncs; ++i)
     if (vcs[i].dtype == dtype && eval_cslice(p, dtype, vcs[i], bud, &cand) &&
-        cand.grid < bud.cus && ceil_div(p.Nc, cand.tc) > 1)
+        cand.grid < bud.cus && ceil_div(p.Nc, cand.tc) > 1) {
+      direct = direct || vcs[i].mode == 2;
       add(cand, CNN_K_SPLITC);
+    }
+  int nsm = 0;
+  const VariantM* vsm = variants_small(&nsm);
+  for (int i = 0; !direct && i < nsm; ++i)
+    if (vsm[i].dtype == dtype && eval_small(p, dtype, vsm[i], bud, &cand)) add(cand, CNN_K_IGEMM);
   if (n == 0) {
     direct_plan(p, dtype, bud, &cand);
     if (cap > 0) out[0] = cand;
@@ -980,6 +1069,16 @@ int select_plan(const cnn_problem& p, int dtype, const cnn_budget& bud, int kern
           v.tc == tc && eval_variant(p, dtype, v, bud, &cand))
         consider(cand, CNN_K_IGEMM);
     }
+    const VariantM* vm = variants_small(&n);  // tc: always Nc
+    for (int i = 0; i < n; ++i)
+      if (vm[i].dtype == dtype && vm[i].tk == tk && vm[i].tp == tp && (tc == 0 || tc == p.Nc) &&
+          eval_small(p, dtype, vm[i], bud, &cand))
+        consider(cand, CNN_K_IGEMM);
+    const VariantT* vt = variants_tile(&n);
+    for (int i = 0; i < n; ++i)
+      if (vt[i].dtype == dtype && vt[i].tk == tk && vt[i].tp == tp && vt[i].tc == tc &&
+          eval_tile(p, dtype, vt[i], 0, bud, &cand))
+        consider(cand, CNN_K_IGEMM);
   } else {
     return CNN_E_UNSUPPORTED;
   }
@@ -1037,6 +1136,9 @@ int list_variants(cnn_variant_t* out, int cap) {
   const VariantQ* vq = variants_srows(&c);
   for (int i = 0; i < c; ++i)
     add(CNN_K_SROWS, vq[i].id, vq[i].dtype, vq[i].nr, vq[i].ns, vq[i].L, vq[i].tk, 0, 16);
+  const VariantM* vm = variants_small(&c);
+  for (int i = 0; i < c; ++i)
+    add(CNN_K_IGEMM, vm[i].id, vm[i].dtype, 0, 0, 0, vm[i].tk, vm[i].tp, 0);
   const VariantT* vt = variants_tile(&c);
   for (int i = 0; i < c; ++i)
     add(CNN_K_IGEMM, vt[i].id, vt[i].dtype, vt[i].nr, vt[i].ns, 0, vt[i].tk, vt[i].tp, vt[i].tc);

@@ -205,6 +205,30 @@ bool tile_geometry(const VariantT& v, const cnn_problem& p, int dtype, int64_t t
 hipError_t launch_tile(const VariantT& v, const void* In, const void* Ker, void* Out,
                        const ConvArgs& a, const TileShape& s, int64_t grid, hipStream_t stream);
 
+// A few-outputs instantiation (conv_small; a CNN_K_IGEMM member): 16 features
+// x tp outputs of one image per workgroup, the contraction shared by its
+// waves; any stencil, strides and feature counts, no workspace.
+struct VariantM {
+  int32_t id;
+  int32_t dtype;
+  int32_t tk;
+  int64_t tp;
+  int32_t acc;
+};
+const VariantM* variants_small(int* count);
+struct SmallShape {
+  int64_t S, LP;       // input rows staged, LDS pitch of a channel (elements)
+  int64_t chk, kpad;   // channels per chunk, its K elements in whole steps
+  int64_t nti, grid;   // tiles per image, workgroups
+  int64_t waves, lds;
+};
+// The instantiation that computes a problem as the direct channel-slice plans
+// (CNN_K_SPLITC, mode 2) describe it: the model's best, nullptr if none fits.
+const VariantM* small_direct(const cnn_problem& p, int dtype, SmallShape* s);
+bool small_geometry(const VariantM& v, const cnn_problem& p, int dtype, SmallShape* s);
+hipError_t launch_small(const VariantM& v, const void* In, const void* Ker, void* Out,
+                        const ConvArgs& a, const SmallShape& s, hipStream_t stream);
+
 // Ker repack for the pipelined kernels (defined with conv_igemm2).
 __global__ void pack_ker_bf16(const uint16_t* __restrict__ Ker, uint32_t __attribute__((ext_vector_type(4)))* __restrict__ P,
                               ConvArgs a, int TK, int TC, int blk_vecs, int64_t total_vecs);

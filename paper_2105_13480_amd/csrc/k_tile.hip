@@ -32,17 +32,14 @@ bool tile_geometry(const VariantT& v, const cnn_problem& p, int dtype, int64_t t
   s->ncol = (p.Nh + ct - 1) / ct;
   s->gather = p.Ns == 1 && p.sh > 1;
   s->squeeze = p.sw >= p.Nr;
-  const int64_t last = p.Nh - (s->ncol - 1) * ct;  // columns of the last band
-  const int64_t cw_l = s->gather ? last : p.sh * (last - 1) + p.Ns;
   s->cw = s->gather ? ct : p.sh * (ct - 1) + p.Ns;
   s->hp = s->gather ? ct : (s->cw + p.sh - 1) / p.sh;
   s->pitch = s->gather ? ct : s->hp * p.sh;
-  // 16-byte items where every band is that wide; pairs need two columns
+  // 16-byte items where a band is that wide; pairs need two columns
   const int64_t epc = 16 / es;
-  const int64_t narrow = std::min(s->cw, cw_l);
-  s->form = narrow < epc || p.sh > 2 ? kPairs : p.sh == 1 ? kWide1 : s->gather ? kGather2 : kWide2;
+  s->form = s->cw < epc || p.sh > 2 ? kPairs : p.sh == 1 ? kWide1 : s->gather ? kGather2 : kWide2;
   s->pw = s->form == kPairs ? 2 : epc;
-  if (narrow < 2) return false;
+  if (s->cw < 2) return false;
   const int64_t rows_total = p.Nb * p.Nw;
   const int64_t rows = tr < rows_total ? tr : rows_total;
   // a run of rows crosses at most this many image boundaries (none where runs
@@ -98,12 +95,8 @@ hipError_t launch_tile(const VariantT& v, const void* In, const void* Ker, void*
   t.ncold = make_fastdiv((uint32_t)s.ncol);
   t.nw = make_fastdiv((uint32_t)a.Nw);
   t.nx = make_fastdiv((uint32_t)a.Nx);
-  const int64_t last = a.Nh - (s.ncol - 1) * s.ct;  // columns of the last band
-  const int64_t cw_l = s.gather ? last : a.sh * (last - 1) + a.Ns;
   t.ipr = make_fastdiv((uint32_t)((s.cw + s.pw - 1) / s.pw));
-  t.ipr_l = make_fastdiv((uint32_t)((cw_l + s.pw - 1) / s.pw));
   t.ctd = make_fastdiv((uint32_t)s.ct);
-  t.ctd_l = make_fastdiv((uint32_t)last);
   t.shd = make_fastdiv((uint32_t)a.sh);
   t.nr = make_fastdiv((uint32_t)a.Nr);
   t.nchd = make_fastdiv((uint32_t)s.nch);

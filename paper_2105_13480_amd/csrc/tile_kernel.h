@@ -61,7 +61,7 @@ struct TileGeo {
   int32_t njt;            // runtime stencils: runs of taps per channel
   int32_t nst;            // stages
   FastDiv kt, ncold, nw, nx, nr, nchd, njd, shd;
-  FastDiv ipr, ctd, ipr_l, ctd_l;  // work items per row and columns of a band, of the last band
+  FastDiv ipr, ctd;       // work items per row and columns of a band
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_t(const void* base, int64_t bytes) {
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (scalar: wave-uniform offsets)
   const int wm = wave / WN, wn = wave % WN;
   const int l32 = lane & 31, half = lane >> 5;
 
@@ -191,11 +191,11 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
   const int k0 = (tile - rest * a.n_ktiles) * TK;
   const int rt = fdiv(rest, t.ncold);
   const int band = rest - rt * t.ncol;
-  const bool last_band = band == t.ncol - 1;
-  const int h0 = band * t.ct;
+  // (the last band may overlap its neighbour: both store the same values there)
+  const int h0 = min(band * t.ct, a.Nh - t.ct);
   const int row0 = rt * t.tr;
   const int rows = min(t.tr, t.rows_total - row0);
-  const int cols = last_band ? a.Nh - h0 : t.ct;
+  const int cols = t.ct;
   const int b0 = fdiv(row0, t.nw);
   const int G0 = b0 * a.Nx + a.sw * (row0 - b0 * a.Nw);  // first input row (flattened b, x)
   int S;                                                  // staged rows
@@ -224,11 +224,10 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
   const uint32_t sel_o = SWAP && swp ? 0x05040100u : 0x07060302u;
   uint32_t voff[MAXP];
   uint32_t dst[MAXP];  // LDS vectors of the item's first two columns, 16 bits each
-  const FastDiv pd = last_band ? t.ipr_l : t.ipr;
 #pragma unroll
   for (int j = 0; j < MAXP; ++j) {
     const int q = min(pt0 + PT * j, nitems - 1);
-    const int row = fdiv(q, pd);
+    const int row = fdiv(q, t.ipr);
     const int col = min(PW * (q - row * ipr), cw - PW);
     int b, x;
     if (t.squeeze) {
@@ -491,12 +490,11 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
   // ---- while stage 0 is on its way: a lane's LDS positions (lanes past the
   // tile's last output take its place)
   const int nout = rows * cols;
-  const FastDiv cd = last_band ? t.ctd_l : t.ctd;
   int pix[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const int q = min((wn * NB + nb) * 32 + l32, nout - 1);
-    const int i = fdiv(q, cd);
+    const int i = fdiv(q, t.ctd);
     int row = i * Nr;
     if (!t.squeeze) {
       const int orow = row0 + i;
@@ -602,6 +600,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
           if constexpr (!PF) fetch_q(std::integral_constant<int, Q>());
           if constexpr (PF && Q + 1 < NSTEP) fetch_q(std::integral_constant<int, Q + 1>());
           multiply(op[Q & 1]);
+          __builtin_amdgcn_sched_barrier(0);
         });
       } else {
         const int q1 = (P + 1) * RS / NP;  // taps multiplied by the end of this part
@@ -615,6 +614,8 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
       }
       if constexpr (MODE >= 1) write(pc, std::integral_constant<bool, MODE == 1>(), st + 1, nxt);
       if constexpr (MODE == 2) load(pc, st + 2);
+      // (keeps the pieces where they are: the scheduler otherwise gathers them)
+      __builtin_amdgcn_sched_barrier(0);
     });
   };
 
@@ -660,7 +661,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         const int q = min((wn * NB + nb) * 32 + l32, nout - 1);
-        const int i = fdiv(q, cd), orow = row0 + i, b = fdiv(orow, t.nw);
+        const int i = fdiv(q, t.ctd), orow = row0 + i, b = fdiv(orow, t.nw);
         io[nb] = (uint32_t)(((int64_t)(b - b0) * a.in_img + (int64_t)(orow - b * a.Nw) * a.sw * a.Ny +
                              (int64_t)(h0 + q - i * cols) * a.sh) * 4);
 #pragma unroll
@@ -714,7 +715,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
 #pragma unroll
   for (int e = 0; e < OPC; ++e) {
     const int q = min(qlast - (OPC - 1) + e, nout - 1);
-    const int i = fdiv(q, cd);
+    const int i = fdiv(q, t.ctd);
     const int orow = row0 + i;
     const int b = fdiv(orow, t.nw);
     oo[e] = (uint32_t)((((int64_t)(b - b0) * a.Nk + k0) * a.hw + (int64_t)(orow - b * a.Nw) * a.Nh +
