@@ -508,7 +508,7 @@ static const double kLaunchUs = 2.0;
 // sums): 1.5 us in a graph replay, 3.6 for a caller that launches one by one
 // (batch-1 1x1 2048 -> 512 at 7x7: 8.8 and 12.4 us split, 10.4 and 10.5 in one
 // launch).
-static const double kSecondLaunchUs = 2.8;
+static const double kSecondLaunchUs = 2.6;
 // HBM writes per byte of Out of the stride-2 row-band kernels (row-piece
 // stores, partial lines), measured with WRITE_SIZE.
 static const double kSrowsWriteRate = 1.18;
