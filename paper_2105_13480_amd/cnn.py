@@ -257,36 +257,56 @@ def fwd_plan_static_ptr(In: int, Ker: int, Out: int, prob: Problem, dtype: int, 
 
 
 def _tensor_dims(In, Ker, Out, sw, sh):
-    import torch
-    for name, t in (("In", In), ("Ker", Ker), ("Out", Out)):
-        if not t.is_cuda or not t.is_contiguous():
-            raise ValueError(f"{name} must be a contiguous GPU tensor")
-        if t.dim() != 4:
-            raise ValueError(f"{name} must be 4-d")
+    # One pass over the tensors' attributes: a call on a small layer is bound by
+    # the host (each attribute read costs about 0.1 us, the kernel 4 us).
+    torch = _torch or _load_torch()
+    if not (In.is_cuda and Ker.is_cuda and Out.is_cuda and In.is_contiguous() and
+            Ker.is_contiguous() and Out.is_contiguous()) or \
+            In.dim() != 4 or Ker.dim() != 4 or Out.dim() != 4:
+        for name, t in (("In", In), ("Ker", Ker), ("Out", Out)):
+            if not t.is_cuda or not t.is_contiguous():
+                raise ValueError(f"{name} must be a contiguous GPU tensor")
+            if t.dim() != 4:
+                raise ValueError(f"{name} must be 4-d")
     Nb, Nc, Nx, Ny = In.shape
     Nk, Nc2, Nr, Ns = Ker.shape
     if Nc2 != Nc or (Nx - Nr) % sw or (Ny - Ns) % sh or Nx < Nr or Ny < Ns:
         raise ValueError("In extent must be sigma*(N-1)+R and channels must agree")
     Nw, Nh = (Nx - Nr) // sw + 1, (Ny - Ns) // sh + 1
-    if tuple(Out.shape) != (Nb, Nk, Nw, Nh):
+    if Out.shape != (Nb, Nk, Nw, Nh):
         raise ValueError(f"Out must have shape {(Nb, Nk, Nw, Nh)}")
-    if In.dtype == torch.float32 and Ker.dtype == torch.float32 and Out.dtype == torch.float32:
-        dt = CNN_F32
-    elif In.dtype == torch.bfloat16 and Ker.dtype == torch.bfloat16:
-        if Out.dtype == torch.float32:
+    di, dk, do = In.dtype, Ker.dtype, Out.dtype
+    if di is torch.bfloat16 and dk is torch.bfloat16:
+        if do is torch.float32:
             dt = CNN_BF16
-        elif Out.dtype == torch.bfloat16:
+        elif do is torch.bfloat16:
             dt = CNN_BF16_OBF16
         else:
             raise ValueError("Out must be float32 or bfloat16")
+    elif di is torch.float32 and dk is torch.float32 and do is torch.float32:
+        dt = CNN_F32
     else:
         raise ValueError("In/Ker must both be float32 or both bfloat16")
     return (Nb, Nc, Nk, Nw, Nh, Nr, Ns, sw, sh), dt
 
 
-def _stream(stream):
+_torch = None
+_raw_stream = None  # current stream of a device as an integer, where torch offers it
+
+
+def _load_torch():
+    global _torch, _raw_stream
     import torch
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _torch = torch
+    return torch
+
+
+def _stream(stream):
     if stream is None:
+        torch = _torch or _load_torch()
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     return getattr(stream, "cuda_stream", stream)
 
@@ -295,7 +315,10 @@ def fwd(In, Ker, Out, sw: int = 1, sh: int = 1, stream=None):
     """Out = conv(In, Ker) on the GPU via cnn_fwd (asynchronous on the
     current torch stream unless ``stream`` is given)."""
     dims, dt = _tensor_dims(In, Ker, Out, sw, sh)
-    fwd_ptr(In.data_ptr(), Ker.data_ptr(), Out.data_ptr(), dims, dt, _stream(stream))
+    st = (_lib or lib()).cnn_fwd(In.data_ptr(), Ker.data_ptr(), Out.data_ptr(), *dims, dt,
+                                 _stream(stream))
+    if st:
+        _check(st)
     return Out
 
 
