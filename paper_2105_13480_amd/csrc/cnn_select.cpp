@@ -34,15 +34,16 @@ static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // Walk the composite tiles of tp outputs; return the largest slab and
 // (optionally) the total number of slab rows over all tiles.
 static int64_t walk_slabs(const cnn_problem& p, int64_t tp, int64_t* total_rows) {
-  const int64_t hw = p.Nw * p.Nh;
-  const int64_t npix = p.Nb * hw;
-  const int64_t Nx = p.sw * (p.Nw - 1) + p.Nr;
+  // In output rows r of the flattened (b, w) index: row b Nx + sw w of In is
+  // sw r + b (Nr - sw).  (Counts below 2^31: 32-bit divisions, a third of the
+  // time of a plan's search.)
+  const uint32_t npix = (uint32_t)(p.Nb * p.Nw * p.Nh), Nh = (uint32_t)p.Nh, Nw = (uint32_t)p.Nw;
+  const uint32_t step = (uint32_t)std::min<int64_t>(tp, npix);
   int64_t mx = 0, tot = 0;
-  for (int64_t f = 0; f < npix; f += tp) {
-    const int64_t last = std::min(f + tp, npix) - 1;
-    const int64_t b0 = f / hw, w0 = (f % hw) / p.Nh;
-    const int64_t b1 = last / hw, w1 = (last % hw) / p.Nh;
-    const int64_t S = (b1 * Nx + p.sw * w1 + p.Nr) - (b0 * Nx + p.sw * w0);
+  for (uint32_t f = 0; f < npix; f += step) {
+    const uint32_t r0 = f / Nh, r1 = (std::min(f + step, npix) - 1) / Nh;
+    const uint32_t b0 = r0 / Nw, b1 = r1 / Nw;
+    const int64_t S = p.sw * (int64_t)(r1 - r0) + p.Nr + (int64_t)(b1 - b0) * (p.Nr - p.sw);
     mx = std::max(mx, S);
     tot += S;
   }
@@ -397,6 +398,9 @@ static bool eval_tile(const cnn_problem& p, int dtype, const VariantT& v, int64_
     double best = 0.0;
     TileShape c;
     for (int64_t r = 1; r <= std::min<int64_t>(v.tp, p.Nb * p.Nw); ++r) {
+      // (as many runs as with one row less, and no whole images: nothing gained)
+      const int64_t R = p.Nb * p.Nw;
+      if (r > 1 && ceil_div(R, r) == ceil_div(R, r - 1) && p.Nw % r != 0 && r % p.Nw != 0) continue;
       if (!tile_geometry(v, p, dtype, r, &c) || c.lds > bud.lds_bytes) continue;
       // narrow bands store and load short pieces of rows: 64 -> 64 features at
       // 224x224, batch 8, in bands of 32 columns 40 us, of 18 columns 51
@@ -741,10 +745,11 @@ void hbm_terms(const cnn_plan_t& pl, int64_t xcds, int64_t l2, double terms[3]) 
     for (int64_t pt = t0 / n_k; pt <= (t1 - 1) / n_k; ++pt) {
       const int64_t f = pt * tp, last = std::min(f + tp, npix) - 1;
       const int64_t r0 = f / p.Nh, r1 = last / p.Nh;  // flattened (b, w) output rows
-      max_slab = std::max(max_slab, (r1 / p.Nw) * Nx + p.sw * (r1 % p.Nw) + p.Nr -
-                                        ((r0 / p.Nw) * Nx + p.sw * (r0 % p.Nw)));
-      for (int64_t r = r0; r <= r1; ++r) {
-        const int64_t g0 = (r / p.Nw) * Nx + p.sw * (r % p.Nw), g1 = g0 + p.Nr;
+      int64_t b = r0 / p.Nw, w = r0 % p.Nw;
+      max_slab = std::max(max_slab, p.sw * (r1 - r0) + p.Nr + (r1 / p.Nw - b) * (p.Nr - p.sw));
+      for (int64_t r = r0; r <= r1; ++r, ++w) {
+        if (w == p.Nw) w = 0, ++b;
+        const int64_t g0 = b * Nx + p.sw * w, g1 = g0 + p.Nr;
         const int64_t from = (end >= 0 && g0 > end && g0 - end <= gap_max) ? end : std::max(g0, end);
         if (g1 > from) rows += g1 - from;
         end = std::max(end, g1);

@@ -273,6 +273,9 @@ const VariantM* variants_small(int* count) {
 bool small_geometry(const VariantM& v, const cnn_problem& p, int dtype, SmallShape* s) {
   const int64_t es = in_bytes(dtype), epc = 16 / es, ks = 4 * epc, RS = p.Nr * p.Ns;
   const int64_t Nx = p.sw * (p.Nw - 1) + p.Nr, Ny = p.sh * (p.Nh - 1) + p.Ns, hw = p.Nw * p.Nh;
+  // 32-bit byte offsets from an image's rows, and into Ker
+  const int64_t lim = 1LL << 31;
+  if (p.Nc * Nx * Ny >= lim / (2 * es) || (p.Nk + 16) * p.Nc * RS >= lim / es) return false;
   // a tile's outputs touch at most this many output rows, so this many input rows
   const int64_t tp = std::min(v.tp, hw);
   const int64_t wr = std::min(p.Nw, (tp - 1 + p.Nh - 1) / p.Nh + 1);
@@ -304,10 +307,7 @@ bool small_geometry(const VariantM& v, const cnn_problem& p, int dtype, SmallSha
   s->lds = std::max(bytes(chk), s->waves * (v.tp / 16) * 1024);
   s->lds = (s->lds + 15) / 16 * 16;
   s->grid = p.Nb * s->nti * ((p.Nk + v.tk - 1) / v.tk);
-  // 32-bit byte offsets from an image's rows, and into Ker
-  const int64_t lim = 1LL << 31;
-  return s->lds <= lds_max && 2 * p.Nc * Nx * Ny * es < lim && (p.Nk + 16) * p.Nc * RS * es < lim &&
-         s->grid <= 0x7fffffffLL;
+  return s->lds <= lds_max && s->grid <= 0x7fffffffLL;
 }
 
 template <int DT, int PB, int KF>

@@ -84,8 +84,8 @@ bool tile_geometry(const VariantT& v, const cnn_problem& p, int dtype, int64_t t
   // 32-bit byte offsets from a tile's first image, and into Ker
   const int64_t imgs = cross + 1;
   const int64_t lim = 1LL << 31;
-  return imgs * p.Nc * Nx * Ny * es < lim && p.Nk * p.Nc * RS * es < lim &&
-         imgs * (p.Nk + 288) * p.Nw * p.Nh * out_bytes(dtype) < lim;
+  return imgs * p.Nc * Nx * Ny < lim / es && p.Nk * p.Nc * RS < lim / es &&
+         imgs * (p.Nk + 288) * p.Nw * p.Nh < lim / out_bytes(dtype);
 }
 
 hipError_t launch_tile(const VariantT& v, const void* In, const void* Ker, void* Out,
