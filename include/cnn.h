@@ -82,13 +82,17 @@ typedef enum cnn_kernel {
   CNN_K_AUTO = 0,     /* let cnn_plan choose                                          */
   CNN_K_DIRECT = 1,   /* one thread per output, fp32 FMA; any shape (correctness path)  */
   CNN_K_IGEMM = 2,    /* implicit GEMM on MFMA, LDS-staged halo'd In slab + Ker tile, any
-                         dtype, stencil and strides, no workspace.  Two kernels:
+                         dtype, stencil and strides, no workspace.  Three kernels:
                          element-wise staging (tiles are runs of tp outputs), and
                          two-dimensional tiles (variants from 3000 on: plan.kc
                          output rows of the flattened (b, w) index by tp/kc
                          columns; 16-byte loads, double-buffered LDS, fp32 as
                          three bf16 parts per value; cnn_plan_tiles: tp = the
-                         instantiation's, the model picks the rows)               */
+                         instantiation's, the model picks the rows); and few
+                         outputs (variants from 3300 on: 16 or 8 features x tp
+                         outputs of one image, the contraction shared by the
+                         workgroup's waves, a fixed order; tc of its plans is Nc,
+                         0 to cnn_plan_tiles)                                     */
   CNN_K_POINTWISE = 3,/* 1x1 stencils, any stride, bf16, Nc % 8 == 0: the inputs of the
                          tile's outputs gathered (no halo, no unused rows), 64 channels
                          per stage, raw Ker rows as in CNN_K_IGEMM_RAWK              */
@@ -154,8 +158,9 @@ typedef enum cnn_kernel {
                          summation order -- and the last bits of Out -- may
                          vary from call to call.  Its direct instantiations
                          (mode = 2; 3x3, either Out type; kc = 1) need none
-                         either: one slice of 128-channel stages per
-                         1024-thread workgroup writes Out in a fixed order */
+                         either: a workgroup takes every channel and writes Out
+                         in a fixed order (on the few-outputs kernel of
+                         CNN_K_IGEMM where 32 channels' rows fit LDS)   */
   CNN_K_AUTO_NO_WORKSPACE = 14 /* (cnn_plan_tiles only) the model's choice among the
                          plans that need no workspace: the plan cnn_fwd runs
                          when no cnn_plan_find result is cached              */

@@ -51,6 +51,10 @@ bool tile_geometry(const VariantT& v, const cnn_problem& p, int dtype, int64_t t
   const int64_t epc = 16 / es;
   s->form = s->cw < epc || p.sh > 2 ? kPairs : p.sh == 1 ? kWide1 : s->gather ? kGather2 : kWide2;
   s->pw = s->form == kPairs ? 2 : epc;
+  // (two loads per item and 128 features on four waves: the registers spill,
+  // 20 us where the model says 12 -- 240 -> 221 features, 1x1 stride 2 at 22x13,
+  // batch 5, 14 us by other plans)
+  if (s->gather && v.nr == 1 && v.tk == 128 && v.waves == 4) return false;
   if (s->cw < 2) return false;
   const int64_t rows_total = p.Nb * p.Nw;
   const int64_t rows = tr < rows_total ? tr : rows_total;

@@ -64,8 +64,10 @@ struct TileGeo {
   FastDiv ipr, ctd;       // work items per row and columns of a band
 };
 
+// (the range ends with the last element's 4-byte word, in memory and not from
+// the base, which may lie at any 2 bytes)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_t(const void* base, int64_t bytes) {
-  bytes = (bytes + 3) & ~(int64_t)3;
+  bytes = (int64_t)((((uintptr_t)base + (uintptr_t)bytes + 3) & ~(uintptr_t)3) - (uintptr_t)base);
   const int32_t n = bytes > 0x7ffffffcLL ? 0x7ffffffc : (int32_t)bytes;
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, n, 0x00020000);
 }

@@ -120,3 +120,33 @@ def test_tile_f32_outside_the_split(dims, case):
         fine = np.isfinite(ref)
         assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
         assert np.abs(got[fine] - ref[fine]).max() <= 1e-5 * scale, pl.variant
+
+
+@pytest.mark.parametrize("mode", list(MODES))
+@pytest.mark.parametrize("dims", [(2, 17, 33, 9, 14, 3, 3, 1, 1), (1, 33, 19, 7, 9, 1, 1, 2, 2),
+                                  (1, 6, 21, 8, 11, 1, 5, 1, 1)], ids=str)
+def test_tensors_at_odd_addresses(dims, mode):
+    """In, Ker and Out that start one element past an aligned address, in both
+    workspace-free kernels that load 16 bytes at any alignment (the tile kernel
+    and the few-outputs kernel, variants 3300 on)."""
+    import torch
+    from gpu_helpers import out_tensor, to_gpu, to_host64
+    Nb, Nc, Nk, Nw, Nh = dims[:5]
+    In, Ker = _ints(dims, mode, seed=sum(dims) + 7)
+    want = oracle.conv(In, Ker, dims[7], dims[8])
+    if mode == "bf16_obf16":
+        want = oracle.widen(inputs.f32_to_bf16_bits(want.astype(np.float32)))
+
+    def shifted(t):
+        whole = torch.zeros(t.numel() + 1, dtype=t.dtype, device="cuda")
+        view = whole[1:].view(t.shape)
+        view.copy_(t)
+        return view
+
+    dIn, dKer = shifted(to_gpu(In)), shifted(to_gpu(Ker))
+    for pl in _tile_plans(dims, mode):
+        dOut = shifted(out_tensor(Nb, Nk, Nw, Nh, mode))
+        say(f"[tile] odd addresses dims={dims} mode={mode} v{pl.variant} rows={pl.kc}")
+        cnn.fwd_plan(dIn, dKer, dOut, pl, dims[7], dims[8])
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host64(dOut), want), pl.variant
