@@ -13,11 +13,9 @@
 //      larger.  This accounts for the P processors of Eq. (2) that the
 //      sequential Eq. (1) leaves out: a tiling with fewer tiles than
 //      workgroup slots leaves CUs idle however little data it moves.
-// The smallest time wins; ties go to the larger tk, then the larger tp,
-// then the larger tc, then the lower instantiation id.  The pipelined bf16
-// kernel (conv_igemm2) is tier 1; the plain staging kernel (conv_igemm) is
-// considered only when no tier-1 instantiation fits; the direct kernel
-// takes problems no implicit-GEMM tiling fits.
+// The smallest time wins; within 2 %, fewer predicted HBM bytes, then fewer
+// Eq. (1) bytes, then the lower instantiation id, then the larger tile.  The
+// direct kernel takes problems no other kernel fits.
 #include <math.h>
 #include <cmath>
 #include <string.h>
