@@ -49,6 +49,14 @@ __host__ __device__ __forceinline__ int fdiv(int n, FastDiv f) {
   return (int)(((uint64_t)(uint32_t)n * f.m) >> f.s);
 }
 
+// Index of a tensor's last element from a tile's first row, for kernels that
+// compare it with 32-bit offsets from there (below 2^30): the tensor may go on
+// for 2^32 elements or more, so it is saturated where no offset reaches, not
+// cut to 32 bits.
+__host__ __device__ __forceinline__ uint32_t last_index(int64_t elems_from_row) {
+  return elems_from_row > 0x7fffffffLL ? 0x7fffffffu : (uint32_t)(elems_from_row - 1);
+}
+
 // The hardware hands consecutive workgroup ids to the 8 XCDs round-robin
 // (id % 8).  Renumber so that each XCD receives one contiguous run of
 // logical tiles: tiles that share input data (the k-tiles of one pixel tile)

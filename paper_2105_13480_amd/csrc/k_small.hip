@@ -90,7 +90,7 @@ __global__ __launch_bounds__(1024) void conv_small(const TI* __restrict__ In,
     ker_last = Ker[(int64_t)a.Nk * a.Nc * RS - 1];
     in_last = In[a.in_total - 1];
   }
-  const uint32_t in_end = (uint32_t)(a.in_total - in0 - 1);  // its index from in0
+  const uint32_t in_end = last_index(a.in_total - in0);  // its index from in0
 
   u32x4_t av[U];
   auto load_a = [&](int c0, int s, int steps) -> u32x4_t {  // (past the end: not used)

@@ -19,11 +19,10 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 
 
-@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
-def test_fastdiv_matches_integer_division():
-    src = os.path.join(ROOT, "tests", "fastdiv", "check_fastdiv.cpp")
+def _check(name):
+    src = os.path.join(ROOT, "tests", "fastdiv", name + ".cpp")
     with tempfile.TemporaryDirectory() as tmp:
-        exe = os.path.join(tmp, "check_fastdiv")
+        exe = os.path.join(tmp, name)
         cmd = [HIPCC, "-O2", "-std=c++17", "-x", "hip", "--offload-arch=gfx950",
                "-I", os.path.join(ROOT, "paper_2105_13480_amd", "csrc"), src, "-o", exe]
         res = subprocess.run(cmd, capture_output=True, text=True)
@@ -31,3 +30,15 @@ def test_fastdiv_matches_integer_division():
         run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
         assert run.returncode == 0, run.stdout + run.stderr
         assert "bad 0" in run.stdout, run.stdout
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_fastdiv_matches_integer_division():
+    _check("check_fastdiv")
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_last_index_past_32_bits():
+    """The few-outputs kernel's patch of In's last element touches no other
+    where 2^32 elements or more follow a tile's first row."""
+    _check("check_last_index")
