@@ -193,8 +193,11 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
   const int k0 = (tile - rest * a.n_ktiles) * TK;
   const int rt = fdiv(rest, t.ncold);
   const int band = rest - rt * t.ncol;
-  // (the last band may overlap its neighbour: both store the same values there)
+  // (the last band may overlap its neighbour.  bf16: both store the same values
+  // there; fp32: the neighbour alone stores them, as one of the two may compute
+  // its tile on the fp32 units, which rounds differently)
   const int h0 = min(band * t.ct, a.Nh - t.ct);
+  const int own = F32 ? band * t.ct - h0 : 0;  // first column of the tile that is stored
   const int row0 = rt * t.tr;
   const int rows = min(t.tr, t.rows_total - row0);
   const int cols = t.ct;
@@ -714,16 +717,19 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
   const int ch = lane % CPR, frow = lane / CPR;
   uint32_t oo[OPC];  // byte offsets of the chunk's outputs, feature k0
   const int qlast = (wn * NB) * 32 + ch * OPC + OPC - 1;
+  uint32_t skip = 0u;  // (fp32) those that the neighbouring band stores, a bit each
 #pragma unroll
   for (int e = 0; e < OPC; ++e) {
     const int q = min(qlast - (OPC - 1) + e, nout - 1);
     const int i = fdiv(q, t.ctd);
+    if (F32 && q - i * cols < own) skip |= 1u << e;
     const int orow = row0 + i;
     const int b = fdiv(orow, t.nw);
     oo[e] = (uint32_t)((((int64_t)(b - b0) * a.Nk + k0) * a.hw + (int64_t)(orow - b * a.Nw) * a.Nh +
                         h0 + q - i * cols) * (int64_t)sizeof(TO));
   }
-  const bool whole = qlast < nout && oo[OPC - 1] - oo[0] == (OPC - 1) * sizeof(TO);
+  const bool whole =
+      qlast < nout && !skip && oo[OPC - 1] - oo[0] == (OPC - 1) * sizeof(TO);
   const uint32_t fbytes = (uint32_t)a.hw * (uint32_t)sizeof(TO);
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
@@ -769,7 +775,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
         } else {
 #pragma unroll
           for (int e = 0; e < OPC; ++e)
-            if (qlast - (OPC - 1) + e < nout) {
+            if (qlast - (OPC - 1) + e < nout && !(skip >> e & 1u)) {
               if constexpr (O16)
                 __builtin_amdgcn_raw_buffer_store_b16(
                     (uint16_t)(v[u][e >> 1] >> (16 * (e & 1))), orr, oo[e] + fo, 0, 0);

@@ -122,6 +122,32 @@ def test_tile_f32_outside_the_split(dims, case):
         assert np.abs(got[fine] - ref[fine]).max() <= 1e-5 * scale, pl.variant
 
 
+@pytest.mark.parametrize("dims", [(1, 32, 40, 5, 300, 3, 3, 1, 1), (1, 32, 40, 3, 290, 1, 1, 1, 1)],
+                         ids=str)
+def test_tile_f32_bands_store_what_they_own(dims):
+    """Bands of columns, the last of which overlaps its neighbour: an infinity
+    in columns that only the last band reads sends that band to the fp32 units,
+    and the outputs of the overlap, which the neighbour owns, keep their bits
+    in every run."""
+    Nh, Ns = dims[4], dims[6]
+    In, Ker = inputs.make_arrays(*dims, "f32", seed_in=21, seed_ker=22,
+                                 in_dist=("uniform", -1.0, 1.0), ker_dist=("he",))
+    bad = In.copy()
+    bad[0, 3, 1, -1] = np.inf  # read by the last output column alone
+    for pl in _tile_plans(dims, "f32"):
+        if pl.variant >= 3300 or Nh % (pl.tp // pl.kc) == 0:
+            continue
+        ct = pl.tp // pl.kc
+        first = Nh // ct * ct  # the last band's own columns
+        assert first < Nh - Ns
+        say(f"[tile] f32 bands dims={dims} v{pl.variant} rows={pl.kc} columns={ct}")
+        clean = run(In, Ker, dims[7], dims[8], "f32", plan=pl)
+        for _ in range(6):
+            got = run(bad, Ker, dims[7], dims[8], "f32", plan=pl)
+            assert np.isinf(got[..., -1]).any()
+            assert np.array_equal(got[..., :first], clean[..., :first]), pl.variant
+
+
 @pytest.mark.parametrize("mode", list(MODES))
 @pytest.mark.parametrize("dims", [(2, 17, 33, 9, 14, 3, 3, 1, 1), (1, 33, 19, 7, 9, 1, 1, 2, 2),
                                   (1, 6, 21, 8, 11, 1, 5, 1, 1)], ids=str)
