@@ -38,8 +38,9 @@
 //   sum to them exactly (truncation, then two roundings: 8 + 8 + 8 bits) and
 //   the six products of combined order up to 2^-16 are accumulated in fp32 by
 //   the bf16 units, 16 times the rate of the fp32 ones.  The parts of infinities
-//   and of values below 2^-102 (other than zero) do not work that way: a
-//   workgroup that met one computes its tile again on the fp32 units.
+//   and of values below 2^-102 (other than zero) do not work that way, nor do
+//   products that overflow: a workgroup that met one computes its tile again on
+//   the fp32 units.
 #pragma once
 
 #include <algorithm>
@@ -646,13 +647,22 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
   }
   stage(std::integral_constant<int, 0>(), st);
   if constexpr (F32) {
-    // Values outside the split's range: the tile again, straight from memory,
-    // two channels a product.  (The buffers are free: each wave's vote there.)
+    // Values outside the split's range, or sums that are not finite (where a
+    // product overflows, a smaller one of its parts may do so with the other
+    // sign: NaN for infinity): the tile again, straight from memory, two
+    // channels a product.  (The buffers are free: each wave's vote there.)
     uint32_t* vote = reinterpret_cast<uint32_t*>(smem);
+    uint32_t top = 0u;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) top = max(top, __float_as_uint(acc[mb][nb][j]) & 0x7fffffffu);
     __syncthreads();
     if (lane == 0) vote[wave] = 0u;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (range.outside()) vote[wave] = 1u;
+    if (range.outside() || top >= 0x7f800000u) vote[wave] = 1u;
     __syncthreads();
     uint32_t any = 0u;
 #pragma unroll

@@ -89,11 +89,11 @@ def test_tile_f32_split_error(dims):
 
 @pytest.mark.parametrize("dims", [(2, 20, 40, 9, 13, 3, 3, 1, 1), (1, 33, 34, 6, 9, 1, 1, 2, 2),
                                   (1, 18, 20, 8, 9, 4, 2, 1, 2)], ids=str)
-@pytest.mark.parametrize("case", ["inf", "nan", "lowest", "tiny", "subnormal"])
+@pytest.mark.parametrize("case", ["inf", "nan", "lowest", "overflow", "tiny", "subnormal"])
 def test_tile_f32_outside_the_split(dims, case):
     """Values that three bf16 parts do not hold: infinities and NaN reach
     exactly the outputs that the direct fp32 kernel's reach, the type's lowest
-    value stays finite, and inputs near the bottom of the range keep fp32's
+    value stays finite, products that overflow are infinite and not NaN, and inputs near the bottom of the range keep fp32's
     relative accuracy."""
     In, Ker = inputs.make_arrays(*dims, "f32", seed_in=8, seed_ker=9,
                                  in_dist=("uniform", 0.25, 1.0), ker_dist=("he",))
@@ -104,6 +104,9 @@ def test_tile_f32_outside_the_split(dims, case):
         In[0, 3, 2, 4] = np.nan
     elif case == "lowest":
         In[0, 3, 2, 4] = np.finfo(np.float32).min
+    elif case == "overflow":  # (1e25 1e25 > 2^144: the lowest parts' products too)
+        In *= np.float32(1e25)
+        Ker = np.abs(Ker) * np.float32(1e25)
     elif case == "tiny":
         In *= np.float32(1e-34)
     else:
@@ -111,7 +114,8 @@ def test_tile_f32_outside_the_split(dims, case):
     prob = cnn.problem(*dims)
     say(f"[tile] f32 {case} dims={dims}: direct kernel")
     ref = run(In, Ker, dims[7], dims[8], "f32", plan=cnn.plan_tiles(prob, cnn.CNN_F32, cnn.K_DIRECT))
-    scale = np.abs(ref[np.isfinite(ref)]).max()
+    scale = np.abs(ref[np.isfinite(ref)]).max(initial=0.0)
+    assert case != "overflow" or np.isposinf(ref).all()
     for pl in _tile_plans(dims, "f32"):
         say(f"[tile] f32 {case} dims={dims} v{pl.variant} rows={pl.kc}")
         got = run(In, Ker, dims[7], dims[8], "f32", plan=pl)
@@ -119,7 +123,7 @@ def test_tile_f32_outside_the_split(dims, case):
         assert np.array_equal(np.isinf(got), np.isinf(ref)), pl.variant
         fine = np.isfinite(ref)
         assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
-        assert np.abs(got[fine] - ref[fine]).max() <= 1e-5 * scale, pl.variant
+        assert np.abs(got[fine] - ref[fine]).max(initial=0.0) <= 1e-5 * scale, pl.variant
 
 
 @pytest.mark.parametrize("dims", [(1, 32, 40, 5, 300, 3, 3, 1, 1), (1, 32, 40, 3, 290, 1, 1, 1, 1)],
