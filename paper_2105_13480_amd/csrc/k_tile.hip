@@ -107,6 +107,7 @@ hipError_t launch_tile(const VariantT& v, const void* In, const void* Ker, void*
   t.njt = (int32_t)s.njt;
   t.njd = make_fastdiv((uint32_t)s.njt);
   t.nst = (a.Nc + (int32_t)v.tc - 1) / (int32_t)v.tc;
+  t.units = v.dtype == CNN_F32 && (int64_t)a.Nc * a.Nr * a.Ns < 8;
   t.kt = make_fastdiv((uint32_t)a.n_ktiles);
   t.ncold = make_fastdiv((uint32_t)s.ncol);
   t.nw = make_fastdiv((uint32_t)a.Nw);

@@ -37,7 +37,16 @@
 // * fp32 (CNN_F32): In and Ker values are split into three bf16 parts that
 //   sum to them exactly (truncation, then two roundings: 8 + 8 + 8 bits) and
 //   the six products of combined order up to 2^-16 are accumulated in fp32 by
-//   the bf16 units, 16 times the rate of the fp32 ones.  The parts of infinities
+//   the bf16 units, 16 times the rate of the fp32 ones; the leading one in a
+//   sum of its own, which is rounded once for 8 channels of a tap where the
+//   fp32 units round for every two.  The error against 64 bits (2-norm, uniform
+//   inputs) is 0.3 to 0.8 of theirs from four products a sum on: 1.2e-7 and
+//   3.5e-7 on 64 channels 3x3, 3.4e-8 and 3.9e-8 on 4 channels 1x1; with one
+//   sum for all six it was 3.5e-7 there, and above theirs (4.0e-8 and 2.6e-8,
+//   1x1, 1 channel; 1.9e-7 and 1.8e-7, 10 channels 3x3) for few channels or
+//   few in the last eight.  What is dropped (up to 4 units of 2^-24 a
+//   product) would show in shorter sums: those below eight products take the
+//   fp32 units.  The parts of infinities
 //   and of values below 2^-102 (other than zero) do not work that way, nor do
 //   products that overflow: a workgroup that met one computes its tile again on
 //   the fp32 units.
@@ -61,6 +70,7 @@ struct TileGeo {
   int32_t nch;            // Ker items per feature and stage (1x1, runtime stencils)
   int32_t njt;            // runtime stencils: runs of taps per channel
   int32_t nst;            // stages
+  int32_t units;          // (fp32) 1: computed on the fp32 units
   FastDiv kt, ncold, nw, nx, nr, nchd, njd, shd;
   FastDiv ipr, ctd;       // work items per row and columns of a band
 };
@@ -510,13 +520,17 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
     pix[nb] = row * t.pitch + q - i * cols + half * t.SP;
   }
 
-  f32x16_t acc[MB][NB];
+  // (fp32: the products of the leading parts, and apart from them the small ones)
+  f32x16_t acc[MB][NB], low[F32 ? MB : 1][F32 ? NB : 1];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) acc[mb][nb][j] = 0.f;
+      for (int j = 0; j < 16; ++j) {
+        acc[mb][nb][j] = 0.f;
+        if constexpr (F32) low[mb][nb][j] = 0.f;
+      }
 
   // One product step's operands: MB blocks of Ker, NB of In (fp32: the Ker
   // values as they are, split when they are used, and the parts of In).
@@ -550,15 +564,20 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
 #pragma unroll
           for (int z = 0; z < 3; ++z) av[mb][z][i] = h.p[z];
         }
-      // the smallest products first
-      constexpr int za[6] = {2, 0, 1, 1, 0, 0}, zb[6] = {0, 2, 1, 0, 1, 0};
+      // the leading parts' product has its own sum, which the others would
+      // round five more times (between them, so that a sum's next product is
+      // not the next one issued: 30.5 us against 30.9 last, 64 -> 64 features
+      // 3x3 at 56x56, batch 16)
+      constexpr int za[6] = {2, 0, 1, 0, 1, 0}, zb[6] = {0, 2, 1, 0, 0, 1};
 #pragma unroll
       for (int z = 0; z < 6; ++z)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-            acc[mb][nb] = mfma_t(av[mb][za[z]], o.b[nb][zb[z]], acc[mb][nb]);
+          for (int nb = 0; nb < NB; ++nb) {
+            f32x16_t& s = z == 3 ? acc[mb][nb] : low[mb][nb];
+            s = mfma_t(av[mb][za[z]], o.b[nb][zb[z]], s);
+          }
     } else {
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
@@ -658,11 +677,14 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) top = max(top, __float_as_uint(acc[mb][nb][j]) & 0x7fffffffu);
+        for (int j = 0; j < 16; ++j) {
+          acc[mb][nb][j] += low[mb][nb][j];
+          top = max(top, __float_as_uint(acc[mb][nb][j]) & 0x7fffffffu);
+        }
     __syncthreads();
     if (lane == 0) vote[wave] = 0u;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (range.outside() || top >= 0x7f800000u) vote[wave] = 1u;
+    if (range.outside() || top >= 0x7f800000u || t.units) vote[wave] = 1u;
     __syncthreads();
     uint32_t any = 0u;
 #pragma unroll
