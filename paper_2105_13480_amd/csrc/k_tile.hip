@@ -116,6 +116,8 @@ hipError_t launch_tile(const VariantT& v, const void* In, const void* Ker, void*
   t.ctd = make_fastdiv((uint32_t)s.ct);
   t.shd = make_fastdiv((uint32_t)a.sh);
   t.nr = make_fastdiv((uint32_t)a.Nr);
+  t.rsd = make_fastdiv((uint32_t)(a.Nr * a.Ns));
+  t.nsd = make_fastdiv((uint32_t)a.Ns);
   t.nchd = make_fastdiv((uint32_t)s.nch);
   for (TileLaunch f : {launch_tile_f32, launch_tile_3x3_bf16, launch_tile_3x3_obf16,
                        launch_tile_any_bf16, launch_tile_any_obf16}) {

@@ -47,9 +47,11 @@
 //   few in the last eight.  What is dropped (up to 4 units of 2^-24 a
 //   product) would show in shorter sums: those below eight products take the
 //   fp32 units.  The parts of infinities
-//   and of values below 2^-102 (other than zero) do not work that way, nor do
-//   products that overflow: a workgroup that met one computes its tile again on
-//   the fp32 units.
+//   do not work that way, nor do products that overflow, and values below
+//   2^-102 (other than zero) lose a part of theirs: a workgroup where that shows
+//   in a sum computes its tile again on the fp32 units (64 -> 64 features 3x3 at
+//   56x56, batch 16: 84 us for 30.5; the fp32 units' staging tiles 82; with unstaged
+//   4-byte loads of Ker the second pass came to 98).
 #pragma once
 
 #include <algorithm>
@@ -71,7 +73,7 @@ struct TileGeo {
   int32_t njt;            // runtime stencils: runs of taps per channel
   int32_t nst;            // stages
   int32_t units;          // (fp32) 1: computed on the fp32 units
-  FastDiv kt, ncold, nw, nx, nr, nchd, njd, shd;
+  FastDiv kt, ncold, nw, nx, nr, nchd, njd, shd, rsd, nsd;
   FastDiv ipr, ctd;       // work items per row and columns of a band
 };
 
@@ -137,8 +139,8 @@ __device__ __forceinline__ Split3 split3(float x, float y) {
   return r;
 }
 
-// Collects what split3 does not cover: infinities and NaNs in `hi`, values
-// other than zero below 2^-102 (whose last part may be subnormal) in `lo`.
+// The largest of the values staged (twice its bits) in `hi`, and in `lo` the
+// least other than zero: below 2^-102 its last part may be subnormal.
 struct SplitRange {
   uint32_t hi = 0u, lo = ~0u;
   __device__ __forceinline__ void see(uint32_t x) {
@@ -146,9 +148,7 @@ struct SplitRange {
     hi = max(hi, m);
     lo = min(lo, m - 1u);  // zero becomes the largest
   }
-  __device__ __forceinline__ bool outside() const {
-    return hi >= (255u << 24) || lo < (25u << 24) - 1u;
-  }
+  __device__ __forceinline__ bool small() const { return lo < (25u << 24) - 1u; }
 };
 
 // TI: bf16_t or float; TO: the Out type.  WM x WN = 4 waves, MB x NB blocks
@@ -666,12 +666,17 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
   }
   stage(std::integral_constant<int, 0>(), st);
   if constexpr (F32) {
-    // Values outside the split's range, or sums that are not finite (where a
-    // product overflows, a smaller one of its parts may do so with the other
-    // sign: NaN for infinity): the tile again, straight from memory, two
-    // channels a product.  (The buffers are free: each wave's vote there.)
-    uint32_t* vote = reinterpret_cast<uint32_t*>(smem);
-    uint32_t top = 0u;
+    // The tile again on the fp32 units, where the parts do not give its sums:
+    // any that is not finite (an infinity or a NaN among its values; or, where
+    // a product overflows, a smaller one of its parts that does so with the
+    // other sign: NaN for infinity), and any that the parts of values below
+    // 2^-102 may have missed.  Such a value's parts lose less than 2^-125 of it
+    // (what is below the least normal number), a sum of K products less than
+    // K 2^-124 top, top the largest value: sums of 2^26 times that keep fp32's
+    // accuracy, so one small weight or input among ordinary ones costs nothing.
+    // (The buffers are free: the votes there.)
+    uint32_t* vote = reinterpret_cast<uint32_t*>(smem);  // [0] recompute, [1] small values, [2] top
+    float nan = 0.f;  // 0 times every sum: NaN if one is not finite
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -679,17 +684,35 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
           acc[mb][nb][j] += low[mb][nb][j];
-          top = max(top, __float_as_uint(acc[mb][nb][j]) & 0x7fffffffu);
+          nan = __builtin_fmaf(acc[mb][nb][j], 0.f, nan);
         }
     __syncthreads();
-    if (lane == 0) vote[wave] = 0u;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (range.outside() || top >= 0x7f800000u || t.units) vote[wave] = 1u;
+    if (tid < 3) vote[tid] = 0u;
     __syncthreads();
-    uint32_t any = 0u;
+    if (nan != 0.f || t.units) vote[0] = 1u;
+    if (range.small()) vote[1] = 1u;
+    __syncthreads();
+    bool again = vote[0] != 0u;
+    if (!again && vote[1]) {
+      atomicMax(&vote[2], range.hi >> 1);
+      float least = __builtin_inff();
 #pragma unroll
-    for (int w = 0; w < NW; ++w) any |= vote[w];
-    if (any) {
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) least = fminf(least, fabsf(acc[mb][nb][j]));
+      __syncthreads();
+      const float bound = (float)(a.Nc * RS) * 0x1p-98f * __uint_as_float(vote[2]);
+      if (!(least >= bound)) vote[0] = 1u;
+      __syncthreads();
+      again = vote[0] != 0u;
+    }
+    if (again) {
+      // Straight from memory: of the flattened (c, r, s) index of a feature, a
+      // lane's half takes four elements of every eight, 16 bytes of Ker and
+      // four gathers of In, two such steps ahead of the products.
+      const int K = a.Nc * RS;
       const uint32_t kmax = (uint32_t)(a.Nk - 1);
       uint32_t ko[MB], io[NB];
 #pragma unroll
@@ -706,29 +729,49 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
 #pragma unroll
           for (int j = 0; j < 16; ++j) acc[mb][nb][j] = 0.f;
       }
-      for (int r = 0; r < Nr; ++r)
-        for (int s = 0; s < Ns; ++s) {
-          const uint32_t kt = (uint32_t)(r * Ns + s) * 4, it = (uint32_t)(r * a.Ny + s) * 4;
-#pragma unroll 4
-          for (int c = half; c < a.Nc + half; c += 2) {
-            const uint32_t cc = (uint32_t)min(c, a.Nc - 1);
-            float av[MB], bv[NB];
+      constexpr int U = 2;
+      struct Raw {
+        u32x4_t a[U][MB];
+        uint32_t b[U][4][NB];
+      };
+      auto fetch_raw = [&](Raw& o, int e0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-              av[mb] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                  kr, ko[mb] + cc * (uint32_t)RS * 4 + kt, 0, 0));
+        for (int u = 0; u < U; ++u) {
+          const int e = e0 + 8 * u + 4 * half;  // (past the end: masked in the products)
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+            o.a[u][mb] = __builtin_bit_cast(
+                u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                             kr, ko[mb] + (uint32_t)min(e, K - 1) * 4, 0, 0));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int x = min(e + i, K - 1), c = fdiv(x, t.rsd), q = x - c * RS, r = fdiv(q, t.nsd);
+            const uint32_t off = (uint32_t)c * plane + (uint32_t)(r * a.Ny + q - r * Ns) * 4;
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
-              bv[nb] = __uint_as_float(
-                  __builtin_amdgcn_raw_buffer_load_b32(ir, io[nb] + cc * plane + it, 0, 0));
+              o.b[u][i][nb] = __builtin_amdgcn_raw_buffer_load_b32(ir, io[nb] + off, 0, 0);
+          }
+        }
+      };
+      Raw cur, nxt;
+      fetch_raw(cur, 0);
+      for (int e0 = 0; e0 < K; e0 += 8 * U) {
+        fetch_raw(nxt, e0 + 8 * U);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const bool in = e0 + 8 * u + 4 * half + i < K;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
               for (int nb = 0; nb < NB; ++nb)
                 acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                    c < a.Nc ? av[mb] : 0.f, c < a.Nc ? bv[nb] : 0.f, acc[mb][nb], 0, 0, 0);
+                    in ? __uint_as_float(cur.a[u][mb][i]) : 0.f,
+                    in ? __uint_as_float(cur.b[u][i][nb]) : 0.f, acc[mb][nb], 0, 0, 0);
           }
-        }
+        cur = nxt;
+      }
     }
   }
   __syncthreads();

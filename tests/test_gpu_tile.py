@@ -160,6 +160,82 @@ def test_tile_f32_outside_the_split(dims, case):
         assert np.abs(got[fine] - ref[fine]).max(initial=0.0) <= 1e-5 * scale, pl.variant
 
 
+@pytest.mark.parametrize("dims", [(2, 20, 40, 9, 13, 3, 3, 1, 1), (2, 33, 34, 6, 9, 1, 1, 2, 2),
+                                  (2, 18, 20, 8, 9, 4, 2, 1, 2)], ids=str)
+@pytest.mark.parametrize("case", ["weight", "channel", "alone", "subnormal alone", "edge", "parts",
+                                  "products"])
+def test_tile_f32_small_values(dims, case):
+    """Values below 2^-102, whose parts are incomplete, and products below the
+    least normal number keep fp32's accuracy in every output, also where they
+    decide it: relative to its own sum of |In Ker| within the bound of the split
+    (one unit of 2^-24 more for what the parts of small values may lose), plus a
+    unit of the smallest number per product."""
+    Nc, RS = dims[1], dims[5] * dims[6]
+    In, Ker = inputs.make_arrays(*dims, "f32", seed_in=31, seed_ker=32,
+                                 in_dist=("uniform", 0.25, 1.0), ker_dist=("he",))
+    In, Ker = In.copy(), Ker.copy()
+    if case == "weight":         # one small weight among ordinary ones
+        Ker[0, 0, 0, 0] = 1e-35
+    elif case == "channel":      # one channel that hardly counts
+        In[:, 3] *= np.float32(1e-36)
+    elif case == "alone":        # an image whose outputs are its small values' alone
+        In[-1] *= np.float32(1e-36)
+        In[-1, 5:] = 0
+    elif case == "subnormal alone":
+        In[-1] = 0
+        In[-1, 3] = np.float32(3e-41)
+    elif case == "edge":         # outputs on either side of where the parts are enough
+        scale = np.exp2(np.linspace(-100, -70, In.shape[3])).astype(np.float32)
+        In *= scale
+        In[:, 2] = np.float32(1e-33)
+    elif case == "parts":        # operands in range, low parts' products below 2^-126
+        In *= np.float32(2.0 ** -60)
+        Ker *= np.float32(2.0 ** -62)
+    else:                        # the products themselves
+        In *= np.float32(2.0 ** -70)
+        Ker *= np.float32(2.0 ** -66)
+    want, absv = oracle.conv(In, Ker, dims[7], dims[8], with_abs=True)
+    units = -(-Nc // 32) * 4 * RS * (1 + 5 / 128) + 6
+    plans = _all_tile_plans(dims, "f32")
+    assert plans
+    for pl in plans:
+        say(f"[tile] f32 small values {case} dims={dims} v{pl.variant} rows={pl.kc}")
+        got = run(In, Ker, dims[7], dims[8], "f32", plan=pl)
+        off = np.abs(got - want) / (units * 2.0 ** -24 * absv + Nc * RS * 2.0 ** -149)
+        assert off.max() <= 1, (pl.variant, off.max())
+
+
+def test_tile_f32_one_small_weight_costs_nothing():
+    """A weight below 2^-102 among ordinary ones does not send the layer to the
+    fp32 units: 3.5 times the time when it did, 1.1 now."""
+    import torch
+    from gpu_helpers import out_tensor, to_gpu
+    dims = (16, 64, 64, 56, 56, 3, 3, 1, 1)
+    In, Ker = inputs.make_arrays(*dims, "f32", seed_in=1, seed_ker=2,
+                                 in_dist=("uniform", 0.0, 1.0), ker_dist=("he",))
+    pl = _tiling(dims, "f32", 64, 256, 16)
+    dIn, dOut = to_gpu(In), out_tensor(*dims[:1], *dims[2:5], "f32")
+
+    def us(k):
+        best = 1e9
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(20):
+                cnn.fwd_plan(dIn, k, dOut, pl, 1, 1)
+            e1.record()
+            e1.synchronize()
+            best = min(best, e0.elapsed_time(e1) * 50)
+        return best
+
+    small = Ker.copy()
+    small[0, 0, 0, 0] = 1e-35
+    say(f"[tile] f32 one small weight v{pl.variant} rows={pl.kc}")
+    plain, tiny = us(to_gpu(Ker)), us(to_gpu(small))
+    say(f"[tile] {plain:.1f} us, {tiny:.1f} us with one small weight")
+    assert tiny <= 2 * plain, (plain, tiny)
+
+
 @pytest.mark.parametrize("dims", [(1, 32, 40, 5, 300, 3, 3, 1, 1), (1, 32, 40, 3, 290, 1, 1, 1, 1)],
                          ids=str)
 def test_tile_f32_bands_store_what_they_own(dims):
