@@ -284,18 +284,10 @@ bool tile_plan_ok(const VariantT& v, const cnn_plan_t& pl, TileShape* s) {
   return pl.slab_rows == s->S && pl.grid == grid && pl.lds_bytes == s->lds && pl.ws_bytes == 0;
 }
 
-const VariantM* find_variant_m(int id) {
-  int n = 0;
-  const VariantM* vs = variants_small(&n);
-  for (int i = 0; i < n; ++i)
-    if (vs[i].id == id) return &vs[i];
-  return nullptr;
-}
-
 // Geometry a few-outputs plan must carry.
 bool small_plan_ok(const VariantM& v, const cnn_plan_t& pl, SmallShape* s) {
-  return small_geometry(v, pl.prob, pl.dtype, s) && pl.slab_rows == s->S && pl.grid == s->grid &&
-         pl.lds_bytes == s->lds && pl.ws_bytes == 0 && pl.tc == pl.prob.Nc;
+  return v.dtype == pl.dtype && v.tk == pl.tk && v.tp == pl.tp && small_geometry(v, pl, s) &&
+         pl.slab_rows == s->S && pl.grid == s->grid && pl.lds_bytes == s->lds && pl.ws_bytes == 0;
 }
 
 // Geometry a plain staging plan (and its split form) must carry: the slab,
@@ -366,8 +358,12 @@ int run_plan(const void* In, const void* Ker, void* Out, const cnn_plan_t& pl, h
     const Variant* v = vc ? nullptr : find_variant(pl.variant);
     const cnn_problem& p = pl.prob;
     const int64_t stages = (p.Nc + pl.tc - 1) / (pl.tc > 0 ? pl.tc : 1);
+    // a direct plan is one of the few-outputs kernel
+    SmallShape ms;
+    const VariantM* vm = vc && vc->mode == 2 ? small_variant(pl) : nullptr;
     const bool match =
-        vc ? vc->dtype == pl.dtype && vc->tk == pl.tk && vc->tp == pl.tp && vc->tc == pl.tc &&
+        vm ? vc->dtype == pl.dtype && cslice_fits(*vc, p) && small_plan_ok(*vm, pl, &ms)
+        : vc ? vc->dtype == pl.dtype && vc->tk == pl.tk && vc->tp == pl.tp && vc->tc == pl.tc &&
                  cslice_geometry_ok(*vc, pl)
            : v && v->kernel == CNN_K_IGEMM && v->dtype == pl.dtype && v->tk == pl.tk &&
                  v->tp == pl.tp && v->tc == pl.tc && igemm_geometry_ok(*v, pl);
@@ -381,14 +377,15 @@ int run_plan(const void* In, const void* Ker, void* Out, const cnn_plan_t& pl, h
                   "(0 for the atomic-sum and direct instantiations; kc = 1 for the direct ones)",
                   (long long)stages);
     if (dry) return CNN_OK;
-    // the direct form on the few-outputs kernel, where that fits: its waves
-    // share the channels, 128 workgroups instead of 16 on the batch-1 deep
-    // layer (bf16 Out: 23.2 -> 11.3 us)
-    SmallShape ms;
-    const VariantM* vm = vc && vc->mode == 2 ? small_direct(p, pl.dtype, &ms) : nullptr;
-    e = vm ? launch_small(*vm, In, Ker, Out, a, ms, st)
-        : vc ? launch_cslice(*vc, In, Ker, Out, ws, a, pl.lds_bytes, pl.kc, pl.dtype, st)
-           : launch_splitc(*v, In, Ker, Out, ws, a, pl.lds_bytes, pl.kc, pl.dtype, st);
+    // (direct plans that carry the 32 x 64 tile, as earlier versions made them,
+    // run that kernel too, in the LDS they name; images and Ker beyond its
+    // 32-bit offsets the one that takes any shape)
+    const bool direct = vc && vc->mode == 2;
+    if (direct && !vm) vm = small_direct(p, pl.dtype, {256, pl.lds_bytes, 128, 2}, &ms);
+    e = vm       ? launch_small(*vm, In, Ker, Out, a, ms, st)
+        : direct ? launch_direct(In, Ker, Out, a, pl.dtype, st)
+        : vc     ? launch_cslice(*vc, In, Ker, Out, ws, a, pl.lds_bytes, pl.kc, pl.dtype, st)
+                 : launch_splitc(*v, In, Ker, Out, ws, a, pl.lds_bytes, pl.kc, pl.dtype, st);
   } else if (pl.kernel == CNN_K_SMALLC) {
     const VariantS* vs = find_variant_s(pl.variant);
     if (!vs || vs->dtype != pl.dtype || vs->tk != pl.tk || !smallc_geometry_ok(*vs, pl))
@@ -415,10 +412,9 @@ int run_plan(const void* In, const void* Ker, void* Out, const cnn_plan_t& pl, h
       return fail(CNN_E_PLAN, "plan names no matching kernel instantiation (variant %d)", pl.variant);
     if (dry) return CNN_OK;
     e = launch_igemm2(*v2, In, Ker, Out, ws, a, pl.lds_bytes, st);
-  } else if (const VariantM* vm = find_variant_m(pl.variant)) {
+  } else if (const VariantM* vm = small_variant(pl)) {
     SmallShape ms;
-    if (pl.kernel != CNN_K_IGEMM || vm->dtype != pl.dtype || vm->tk != pl.tk || vm->tp != pl.tp ||
-        !small_plan_ok(*vm, pl, &ms))
+    if (!small_plan_ok(*vm, pl, &ms))
       return fail(CNN_E_PLAN, "plan names no matching kernel instantiation (variant %d)", pl.variant);
     if (dry) return CNN_OK;
     e = launch_small(*vm, In, Ker, Out, a, ms, st);

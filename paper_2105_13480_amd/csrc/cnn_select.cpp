@@ -434,14 +434,13 @@ static const VariantT* tile_variant(int kernel, int id) {
   return nullptr;
 }
 
-// Few-outputs kernel (conv_small).
-static bool eval_small(const cnn_problem& p, int dtype, const VariantM& v, const cnn_budget& bud,
-                       cnn_plan_t* plan) {
-  SmallShape s;
-  // few outputs: up to four workgroups per CU (with 20 per CU a 3-channel
-  // 3x3 stride-2 layer ran 30 us against 19 on the few-channel kernel)
-  if (!small_geometry(v, p, dtype, &s) || s.grid > 4 * bud.cus) return false;
-  if (!eval_tiling(p, dtype, v.id, v.tk, v.tp, p.Nc, v.acc, s.S, s.lds, 0, bud, plan)) return false;
+// The few-outputs kernel's plan with the geometry s.
+static bool small_plan(const cnn_problem& p, int dtype, int id, const VariantM& v,
+                       const SmallShape& s, const cnn_budget& bud, cnn_plan_t* plan) {
+  if (!eval_tiling(p, dtype, id, v.tk, v.tp, p.Nc, v.acc, s.S, s.lds, 0, bud, plan)) return false;
+  // (tc: Nc unless the budget asks for smaller chunks than LDS holds)
+  SmallShape whole;
+  if (small_geometry(v, p, dtype, 160 * 1024, 0, &whole) && whole.chk != s.chk) plan->tc = s.chk;
   plan->grid = s.grid;
   const double ks = dtype == CNN_F32 ? 16 : 32;
   plan->mfma_flops = 2.0 * 16 * v.tp * std::ceil((double)(p.Nc * p.Nr * p.Ns) / ks) * ks *
@@ -449,11 +448,32 @@ static bool eval_small(const cnn_problem& p, int dtype, const VariantM& v, const
   return true;
 }
 
-static const VariantM* small_variant(int kernel, int id) {
+// Few-outputs kernel (conv_small).
+static bool eval_small(const cnn_problem& p, int dtype, const VariantM& v, const cnn_budget& bud,
+                       cnn_plan_t* plan) {
+  SmallShape s;
+  // few outputs: up to four workgroups per CU (with 20 per CU a 3-channel
+  // 3x3 stride-2 layer ran 30 us against 19 on the few-channel kernel)
+  return small_geometry(v, p, dtype, bud.lds_bytes, 0, &s) && s.grid <= 4 * bud.cus &&
+         small_plan(p, dtype, v.id, v, s, bud, plan);
+}
+
+static bool direct_slices(const cnn_plan_t& pl) {  // a plan of CNN_K_SPLITC, mode 2
+  int n = 0;
+  const VariantC* vc = variants_cslice(&n);
+  for (int i = 0; pl.kernel == CNN_K_SPLITC && i < n; ++i)
+    if (vc[i].id == pl.variant) return vc[i].mode == 2;
+  return false;
+}
+
+const VariantM* small_variant(const cnn_plan_t& pl) {
+  const bool direct = direct_slices(pl);
   int n = 0;
   const VariantM* vm = variants_small(&n);
-  for (int i = 0; kernel == CNN_K_IGEMM && i < n; ++i)
-    if (vm[i].id == id) return &vm[i];
+  for (int i = 0; i < n; ++i)
+    if (direct ? vm[i].dtype == pl.dtype && vm[i].tk == pl.tk && vm[i].tp == pl.tp
+               : pl.kernel == CNN_K_IGEMM && vm[i].id == pl.variant)
+      return &vm[i];
   return nullptr;
 }
 
@@ -478,15 +498,15 @@ static double small_us(const cnn_problem& p, int dtype, const VariantM& v, const
   return 1.75 + odd * (double)(n / occ) * round((double)occ) + odd * (n % occ ? round((double)(n % occ)) : 0.0);
 }
 
-const VariantM* small_direct(const cnn_problem& p, int dtype, SmallShape* s) {
-  const cnn_budget bud = {256, 160 * 1024, 128, 2};
+const VariantM* small_direct(const cnn_problem& p, int dtype, const cnn_budget& bud,
+                             SmallShape* s) {
   const VariantM* best = nullptr;
   double tb = 0.0;
   int n = 0;
   const VariantM* vm = variants_small(&n);
   for (int i = 0; i < n; ++i) {
     SmallShape c;
-    if (vm[i].dtype != dtype || !small_geometry(vm[i], p, dtype, &c)) continue;
+    if (vm[i].dtype != dtype || !small_geometry(vm[i], p, dtype, bud.lds_bytes, 0, &c)) continue;
     const double t = small_us(p, dtype, vm[i], c, bud);
     if (!best || t < tb) best = &vm[i], tb = t, *s = c;
   }
@@ -573,12 +593,9 @@ static FamilyCost family_cost(int kernel, int variant, int dtype) {
     case CNN_K_SPLITC: {
       int n = 0;
       const VariantC* vc = variants_cslice(&n);
-      // a stage's loads at once; atomic sums cost 1.3 us more; the direct
-      // form's 128-channel stages (one 1024-thread workgroup per CU) run
-      // about 5 us each, bound by one CU's outstanding requests
+      // a stage's loads at once; atomic sums cost 1.3 us more
       for (int i = 0; i < n; ++i)
-        if (vc[i].id == variant)
-          return {0.50, vc[i].mode == 1 ? 2.30 : 1.00, vc[i].mode == 2 ? 2.90 : 1.50, 50.0};
+        if (vc[i].id == variant) return {0.50, vc[i].mode == 1 ? 2.30 : 1.00, 1.50, 50.0};
       return dtype == CNN_F32 ? FamilyCost{0.51, 3.07, 1.65, 4.1} : FamilyCost{0.121, 4.59, 1.89, 3.71};
     }
     case CNN_K_IGEMM:
@@ -619,22 +636,10 @@ static double model_us(const cnn_plan_t& pl, const cnn_budget& bud, double w_out
                          ? tile_us(p, pl.dtype, *v, s, bud) : 0.0;
     return std::max(t, pl.hbm_bytes / (hbm_gbs(w_out) * 1e3) + kLaunchUs);
   }
-  if (const VariantM* v = small_variant(pl.kernel, pl.variant)) {
+  if (const VariantM* v = small_variant(pl)) {
     SmallShape s;
-    const double t = small_geometry(*v, p, pl.dtype, &s) ? small_us(p, pl.dtype, *v, s, bud) : 0.0;
+    const double t = small_geometry(*v, pl, &s) ? small_us(p, pl.dtype, *v, s, bud) : 0.0;
     return std::max(t, pl.hbm_bytes / (hbm_gbs(w_out) * 1e3) + kLaunchUs);
-  }
-  if (pl.kernel == CNN_K_SPLITC && pl.kc == 1 && pl.ws_bytes == 0) {
-    int n = 0;
-    const VariantC* vc = variants_cslice(&n);
-    for (int i = 0; i < n; ++i) {
-      SmallShape s;
-      const VariantM* v = vc[i].id == pl.variant && vc[i].mode == 2
-                              ? small_direct(p, pl.dtype, &s) : nullptr;
-      if (v)
-        return std::max(small_us(p, pl.dtype, *v, s, bud),
-                        pl.hbm_bytes / (hbm_gbs(w_out) * 1e3) + kLaunchUs);
-    }
   }
   const double kc = pl.kernel == CNN_K_SPLITC ? (double)pl.kc : 1.0;
   const double wgs = (double)pl.grid * kc;
@@ -768,7 +773,8 @@ void hbm_terms(const cnn_plan_t& pl, int64_t xcds, int64_t l2, double terms[3]) 
     ker_b += set + (double)max_slab * row_bytes <= (double)l2 ? set : per_tile;
   }
   const double out = (double)npix * (double)p.Nk;
-  terms[0] = e_out * out + (pl.kernel == CNN_K_SPLITC ? 8.0 * pl.kc * out : 0.0);
+  terms[0] = e_out * out +
+             (pl.kernel == CNN_K_SPLITC && !direct_slices(pl) ? 8.0 * pl.kc * out : 0.0);
   // The stride-2 row-band kernels store Out as row pieces (Nh values per
   // feature row) that rarely fill a 128-byte line; the L2 merges most
   // neighbouring pieces but writes some lines twice: measured WRITE_SIZE is
@@ -841,7 +847,11 @@ static bool eval_cslice(const cnn_problem& p, int dtype, const VariantC& v,
   if (!eval_tiling(p, dtype, v.id, v.tk, v.tp, v.tc, 16, S, lds, 0, bud, plan)) return false;
   splitc_finish(p, bud, plan);
   if (v.mode == 1) plan->ws_bytes = 0;  // the slices add into Out
-  if (v.mode == 2) {                     // one slice writing Out
+  if (v.mode == 2) {                     // one slice writing Out: the few-outputs kernel's plan
+    SmallShape s;
+    const VariantM* m = small_direct(p, dtype, bud, &s);
+    if (m && !small_plan(p, dtype, v.id, *m, s, bud, plan)) return false;
+    plan->kernel = CNN_K_SPLITC;
     plan->kc = 1;
     plan->ws_bytes = 0;
   }
@@ -935,8 +945,10 @@ int enumerate_plans(const cnn_problem& p, int dtype, const cnn_budget& bud, cnn_
   const VariantC* vcs = variants_cslice(&ncs);
   bool direct = false;  // the direct channel-slice plan stands for the few-outputs kernel
   for (int i = 0; i < ncs; ++i)
-    if (vcs[i].dtype == dtype && eval_cslice(p, dtype, vcs[i], bud, &cand) &&
-        cand.grid < bud.cus && ceil_div(p.Nc, cand.tc) > 1) {
+    if (vcs[i].dtype == dtype &&
+        ceil_div(p.Nb * p.Nw * p.Nh, vcs[i].tp) * ceil_div(p.Nk, vcs[i].tk) < bud.cus &&
+        ceil_div(p.Nc, vcs[i].tc) > 1 && eval_cslice(p, dtype, vcs[i], bud, &cand)) {
+      if (vcs[i].mode == 2 && !small_variant(cand)) continue;  // (beyond its 32-bit offsets)
       direct = direct || vcs[i].mode == 2;
       add(cand, CNN_K_SPLITC);
     }

@@ -222,10 +222,19 @@ struct SmallShape {
   int64_t nti, grid;   // tiles per image, workgroups
   int64_t waves, lds;
 };
-// The instantiation that computes a problem as the direct channel-slice plans
-// (CNN_K_SPLITC, mode 2) describe it: the model's best, nullptr if none fits.
-const VariantM* small_direct(const cnn_problem& p, int dtype, SmallShape* s);
-bool small_geometry(const VariantM& v, const cnn_problem& p, int dtype, SmallShape* s);
+// The model's best instantiation for a problem (the direct channel-slice plans,
+// CNN_K_SPLITC mode 2, stand for it), nullptr if none fits.
+const VariantM* small_direct(const cnn_problem& p, int dtype, const cnn_budget& bud, SmallShape* s);
+// The instantiation a plan names (one of CNN_K_IGEMM, or CNN_K_SPLITC mode 2),
+// nullptr if none.
+const VariantM* small_variant(const cnn_plan_t& pl);
+// Its geometry in chunks of chk channels (0: as many as fit lds_max bytes).
+bool small_geometry(const VariantM& v, const cnn_problem& p, int dtype, int64_t lds_max,
+                    int64_t chk, SmallShape* s);
+// ... and of a finished plan: its tc is the chunk (Nc: as many as fit LDS).
+inline bool small_geometry(const VariantM& v, const cnn_plan_t& pl, SmallShape* s) {
+  return small_geometry(v, pl.prob, pl.dtype, 160 * 1024, pl.tc == pl.prob.Nc ? 0 : pl.tc, s);
+}
 hipError_t launch_small(const VariantM& v, const void* In, const void* Ker, void* Out,
                         const ConvArgs& a, const SmallShape& s, hipStream_t stream);
 
@@ -286,10 +295,11 @@ hipError_t launch_splitc_reduce(const float* Part, void* Out, int kc, int64_t n,
 // A channel-slice instantiation (bf16, fixed stencil): tiles of tk = 32
 // features x tp = 64 outputs over one slice of the channels, tc = 32
 // channels per stage, every load of a stage in flight at once; fp32 partial
-// tiles in the workspace, then the ordered reduce (mode 0); fp32 atomic
-// adds into Out after a zero fill (mode 1: no workspace, fp32 Out only); or
-// one slice (kc = 1) of 128-channel stages writing Out directly (mode 2: no
-// workspace, any Out type).  A CNN_K_SPLITC family member beside the
+// tiles in the workspace, then the ordered reduce (mode 0); or fp32 atomic
+// adds into Out after a zero fill (mode 1: no workspace, fp32 Out only).  Mode
+// 2 (one slice writing Out, no workspace, any Out type) names plans of the
+// few-outputs kernel: cnn_plan_tiles takes tk 32, tp 64 and tc 128 for them, the
+// plan's own are the launch's.  A CNN_K_SPLITC family member beside the
 // CNN_K_IGEMM split form.
 struct VariantC {
   int32_t id;

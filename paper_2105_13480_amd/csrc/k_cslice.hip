@@ -6,8 +6,7 @@
 //
 // Workgroup (tile, z) owns 32 output features x 64 consecutive outputs of the
 // flattened (b, w, h) index (the paper's composite T_bhw) and the channels
-// [z*cs, z*cs + cs) of slice z, in stages of TC = 16, 32, 64 or 128
-// channels.  A stage issues all of its global loads before it waits on any:
+// [z*cs, z*cs + cs) of slice z, in stages of TC = 16, 32 or 64 channels.  A stage issues all of its global loads before it waits on any:
 // the tile's Ker rows (32 features x TC channels x all taps, 16-byte loads of
 // the rows as they lie, one feature's 8 channels per thread) and the halo'd
 // In slab of the tile ((position, 8-channel group) tasks spread over all
@@ -37,15 +36,11 @@
 // (splitc_reduce) then writes Out, so the result does not depend on which
 // workgroup finishes first.
 //
-// Workspace-free instantiations:
-//   atomic (MODE 1, fp32 Out): a fill kernel zeroes Out, then every slice
-//     adds its partial tile into Out with fp32 atomic adds.  The sum is then
-//     formed in the order the workgroups arrive, so the last bits of Out may
-//     differ from call to call (integer-valued sums excepted: they are exact
-//     in any order);
-//   direct (MODE 2, any Out type): one slice (kc = 1) of 128-channel stages
-//     on 1024-thread workgroups (eight K groups), each workgroup walking all
-//     channels of its tile and writing Out itself, in a fixed order.
+// Workspace-free instantiations (MODE 1, fp32 Out): a fill kernel zeroes Out,
+// then every slice adds its partial tile into Out with fp32 atomic adds.  The
+// sum is then formed in the order the workgroups arrive, so the last bits of
+// Out may differ from call to call (integer-valued sums excepted: they are
+// exact in any order).
 #include "internal.h"
 #include "common.h"
 
@@ -81,14 +76,14 @@ template <int TC> struct CsliceShape {
 };
 
 // MODE 0: fp32 partial tiles to slice z of Dst (the workspace); 1: fp32
-// atomic adds into Dst (Out, zeroed); 2: TO values into Dst (Out), kc = 1.
-template <int NR, int NS, int TC, int MODE, typename TO>
+// atomic adds into Dst (Out, zeroed).
+template <int NR, int NS, int TC, int MODE>
 __global__ __launch_bounds__(CsliceShape<TC>::NT) void conv_cslice(const bf16_t* __restrict__ In,
                                                    const bf16_t* __restrict__ Ker,
-                                                   void* __restrict__ Dst, ConvArgs a, int cs,
+                                                   float* __restrict__ Dst, ConvArgs a, int cs,
                                                    FastDiv dv_nxny) {
   constexpr int T = NR * NS;
-  constexpr int kTC = TC;          // channels per stage (16, 32, 64 or 128)
+  constexpr int kTC = TC;          // channels per stage (16, 32 or 64)
   constexpr int kCG = kTC / 8;     // 8-channel groups per stage
   constexpr int kIPV = kCG + 1;    // 16-byte vectors per In position in LDS (one pad)
   constexpr int NK = CsliceShape<TC>::NK, NT = CsliceShape<TC>::NT;
@@ -144,8 +139,7 @@ __global__ __launch_bounds__(CsliceShape<TC>::NT) void conv_cslice(const bf16_t*
   const int c_end = min(a.Nc, c_begin + cs);
   for (int c0 = c_begin; c0 < c_end; c0 += kTC) {
     const int ncg = min(kTC, c_end - c0) >> 3;  // even (Nc and cs are multiples of 16)
-    static_assert(kTC == 16 || kTC == 32 || kTC == 64 || kTC == 128,
-                  "stages of 16, 32, 64 or 128 channels");
+    static_assert(kTC == 16 || kTC == 32 || kTC == 64, "stages of 16, 32 or 64 channels");
     // Every global load of the stage, Ker first.
     u32x4_t kr[T];
     const bool kload = ktask && kcg < ncg;
@@ -229,7 +223,7 @@ __global__ __launch_bounds__(CsliceShape<TC>::NT) void conv_cslice(const bf16_t*
   }
   __syncthreads();
   if (kh == 0) {
-    float* dst = static_cast<float*>(Dst) + (MODE == 0 ? (int64_t)blockIdx.y * a.out_total : 0);
+    float* dst = Dst + (MODE == 0 ? (int64_t)blockIdx.y * a.out_total : 0);
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const int k = k0 + 8 * (j >> 2) + 4 * half + (j & 3);
@@ -239,8 +233,6 @@ __global__ __launch_bounds__(CsliceShape<TC>::NT) void conv_cslice(const bf16_t*
       if (pval && k < a.Nk) {
         if constexpr (MODE == 1)
           unsafeAtomicAdd(dst + obase + (int64_t)k * a.hw, v);  // hardware fp32 add
-        else if constexpr (MODE == 2)
-          static_cast<TO*>(Dst)[obase + (int64_t)k * a.hw] = from_f32<TO>(v);
         else
           dst[obase + (int64_t)k * a.hw] = v;
       }
@@ -251,8 +243,7 @@ __global__ __launch_bounds__(CsliceShape<TC>::NT) void conv_cslice(const bf16_t*
 // ---- instantiation table ------------------------------------------------
 // X(id, dtype, Nr, Ns, tc, mode): mode 0 (partials and the ordered reduce)
 // is the same kernel for both bf16 dtypes (the reduce writes the Out type);
-// mode 1 (atomic sums) needs fp32 Out; mode 2 (direct, kc = 1) writes the
-// dtype's Out type.
+// mode 1 (atomic sums) needs fp32 Out.
 #define CNN_CSLICE_VARIANTS(X)           \
   X(2500, CNN_BF16, 3, 3, 32, 0)         \
   X(2501, CNN_BF16_OBF16, 3, 3, 32, 0)   \
@@ -263,13 +254,15 @@ __global__ __launch_bounds__(CsliceShape<TC>::NT) void conv_cslice(const bf16_t*
   X(2506, CNN_BF16, 3, 3, 64, 0)         \
   X(2507, CNN_BF16_OBF16, 3, 3, 64, 0)   \
   X(2508, CNN_BF16, 3, 3, 32, 1)         \
-  X(2509, CNN_BF16, 1, 1, 32, 1)         \
+  X(2509, CNN_BF16, 1, 1, 32, 1)
+// Mode 2 (one slice, Out written directly): plans of the few-outputs kernel.
+#define CNN_CSLICE_DIRECT(X)             \
   X(2510, CNN_BF16, 3, 3, 128, 2)        \
   X(2511, CNN_BF16_OBF16, 3, 3, 128, 2)
 
 static const VariantC kVariantsC[] = {
 #define CNN_ROW(id, dt, nr, ns, tc, mode) {id, dt, kTK, kTP, tc, nr, ns, mode},
-    CNN_CSLICE_VARIANTS(CNN_ROW)
+    CNN_CSLICE_VARIANTS(CNN_ROW) CNN_CSLICE_DIRECT(CNN_ROW)
 #undef CNN_ROW
 };
 
@@ -296,17 +289,11 @@ __global__ __launch_bounds__(256) void cslice_zero(float* __restrict__ Out, int6
   for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < n; o += stride) Out[o] = 0.f;
 }
 
-// Out element type of an instantiation: fp32 except the direct form of
-// the bf16-Out dtype.
-template <int DT, int MODE> struct CsliceOut { typedef float T; };
-template <> struct CsliceOut<CNN_BF16_OBF16, 2> { typedef bf16_t T; };
-
-// dst: the partial slices (mode 0), or Out itself (mode 1: zeroed first;
-// mode 2: written once).
-template <int NR, int NS, int TC, int MODE, typename TO>
+// dst: the partial slices (mode 0), or Out itself (mode 1: zeroed first).
+template <int NR, int NS, int TC, int MODE>
 static hipError_t launch_one_c(const void* In, const void* Ker, void* dst, const ConvArgs& a,
                                int64_t lds, int kc, int cs, hipStream_t stream) {
-  auto kern = conv_cslice<NR, NS, TC, MODE, TO>;
+  auto kern = conv_cslice<NR, NS, TC, MODE>;
   if (lds > 64 * 1024) {
     const hipError_t e = allow_max_lds((const void*)kern);
     if (e != hipSuccess) return e;
@@ -319,7 +306,7 @@ static hipError_t launch_one_c(const void* In, const void* Ker, void* dst, const
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)a.grid, (unsigned)kc), dim3(CsliceShape<TC>::NT),
                      (unsigned)lds,
-                     stream, (const bf16_t*)In, (const bf16_t*)Ker, dst, a, cs,
+                     stream, (const bf16_t*)In, (const bf16_t*)Ker, (float*)dst, a, cs,
                      make_fastdiv((uint32_t)a.nxny));
   return hipGetLastError();
 }
@@ -332,8 +319,7 @@ hipError_t launch_cslice(const VariantC& v, const void* In, const void* Ker, voi
   switch (v.id) {
 #define CNN_CASE(id, dt, nr, ns, tc, mode)                                              \
   case id:                                                                               \
-    e = launch_one_c<nr, ns, tc, mode, CsliceOut<dt, mode>::T>(In, Ker, mode ? Out : ws, a, \
-                                                               lds_bytes, kc, cs, stream); \
+    e = launch_one_c<nr, ns, tc, mode>(In, Ker, mode ? Out : ws, a, lds_bytes, kc, cs, stream); \
     break;
     CNN_CSLICE_VARIANTS(CNN_CASE)
 #undef CNN_CASE

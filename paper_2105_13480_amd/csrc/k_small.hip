@@ -275,8 +275,10 @@ const VariantM* variants_small(int* count) {
   return kVariantsM;
 }
 
-// The geometry of instantiation v; false if it does not fit.
-bool small_geometry(const VariantM& v, const cnn_problem& p, int dtype, SmallShape* s) {
+// The geometry of instantiation v in chunks of chk channels (0: as many as fit
+// lds_max bytes); false if it does not fit.
+bool small_geometry(const VariantM& v, const cnn_problem& p, int dtype, int64_t lds_max,
+                    int64_t chk, SmallShape* s) {
   const int64_t es = in_bytes(dtype), epc = 16 / es, ks = 4 * epc, RS = p.Nr * p.Ns;
   const int64_t Nx = p.sw * (p.Nw - 1) + p.Nr, Ny = p.sh * (p.Nh - 1) + p.Ns, hw = p.Nw * p.Nh;
   // 32-bit byte offsets from an image's rows, and into Ker
@@ -287,14 +289,16 @@ bool small_geometry(const VariantM& v, const cnn_problem& p, int dtype, SmallSha
   const int64_t wr = std::min(p.Nw, (tp - 1 + p.Nh - 1) / p.Nh + 1);
   s->S = std::min(Nx, p.sw * (wr - 1) + p.Nr);
   const int64_t LP = (s->S * Ny + epc - 1) / epc * epc;
-  // the largest chunk (whole 32-channel groups, or all channels) whose slab
-  // fits LDS with its offset table
-  const int64_t lds_max = 160 * 1024;
+  // a chunk is whole 32-channel groups, or all channels; its slab and offset
+  // table fit LDS
+  lds_max = std::min<int64_t>(lds_max, 160 * 1024);
   auto bytes = [&](int64_t c) {
     return c * LP * es + (c * RS + ks - 1) / ks * ks * 4;
   };
   auto fits = [&](int64_t c) { return bytes(c) <= lds_max; };
-  int64_t chk = p.Nc;
+  if (chk == 0) chk = p.Nc;
+  else if (chk < 1 || chk > p.Nc || (chk < p.Nc && chk % 32)) return false;
+  else if (!fits(chk)) return false;
   if (!fits(chk)) {
     const int64_t n = lds_max / (LP * es + RS * 4) / 32;
     if (n < 1) return false;

@@ -430,6 +430,40 @@ def test_channel_slice_plans():
         assert st == -8, pl.variant
 
 
+@pytest.mark.parametrize("dtype", [1, 2])
+def test_direct_slice_plans_describe_their_launch(dtype):
+    """The direct channel-slice plans are the few-outputs kernel's: features,
+    outputs, workgroups, LDS and rows equal those of its own plan by the same
+    tile, no partial Outs are counted, a budget's LDS holds, and a slice count
+    other than one or a tile that is not a launch's is refused before HIP."""
+    L = cnn.lib()
+    for dims in [(1, 512, 512, 7, 7, 3, 3, 1, 1), (1, 1024, 512, 7, 7, 3, 3, 1, 1),
+                 (2, 160, 45, 5, 9, 3, 3, 2, 1), (1, 256, 70, 1, 60, 3, 3, 1, 1)]:
+        p = cnn.problem(*dims)
+        for lds in (160 * 1024, 130 * 1024):
+            bud = cnn.budget(lds_bytes=lds)
+            pl = cnn.plan_tiles(p, dtype, cnn.K_SPLITC, 32, 64, 128, bud)
+            own = cnn.plan_tiles(p, dtype, cnn.K_IGEMM, pl.tk, pl.tp, 0, bud)
+            assert pl.variant == 2509 + dtype and 3300 <= own.variant < 3400
+            for f in ("tk", "tp", "tc", "grid", "lds_bytes", "slab_rows", "ws_bytes", "mfma_flops"):
+                assert getattr(pl, f) == getattr(own, f), f
+            assert pl.lds_bytes <= lds
+            assert cnn.hbm_bytes(pl) == cnn.hbm_bytes(own)
+            assert (pl.variant, pl.tp) in {(c.variant, c.tp) for c in cnn.plan_candidates(p, dtype, bud)}
+            for change in ({"kc": 2}, {"tp": 48}, {"grid": pl.grid + 1}, {"tc": 96 if pl.tc != 96 else 64},
+                           {"lds_bytes": pl.lds_bytes - 16}):
+                q = cnn.Plan.from_buffer_copy(pl)
+                for k, v in change.items():
+                    setattr(q, k, v)
+                st = L.cnn_fwd_plan_ws(0x1000, 0x40000000, 0x80000000, ctypes.byref(p), dtype,
+                                       ctypes.byref(q), None, 0, None)
+                assert st == -8, change
+    # beyond that kernel's 32-bit offsets the request is still accepted
+    far = cnn.plan_tiles(cnn.problem(1, 1 << 25, 32, 1, 1, 3, 3, 1, 1), dtype, cnn.K_SPLITC, 32, 64,
+                         128, cnn.budget())
+    assert (far.variant, far.tk, far.tp, far.tc) == (2509 + dtype, 32, 64, 128)
+
+
 def test_workspace_plans_need_the_workspace_form():
     """cnn_fwd_plan never allocates: a plan that needs a workspace is
     refused before any HIP call; cnn_fwd_plan_ws checks the workspace."""

@@ -54,21 +54,25 @@ def test_small_exact_integers(dims, mode):
 
 
 @pytest.mark.parametrize("mode", ["bf16", "bf16_obf16"])
-def test_direct_slices_where_the_rows_do_not_fit(mode):
-    """The direct channel-slice plan runs the few-outputs kernel where 32
-    channels' rows fit LDS and its own kernel elsewhere: the two agree with
-    the oracle on either side of that line."""
-    for dims in [(1, 160, 32, 1, 60, 3, 3, 1, 1), (1, 160, 32, 1, 800, 3, 3, 1, 1)]:
-        In, Ker = inputs.make_arrays(*dims, "bf16", seed_in=3, seed_ker=4, in_dist=("int", -2, 2),
-                                     ker_dist=("int", -2, 2))
-        want = oracle.conv(In, Ker, 1, 1)
-        if mode == "bf16_obf16":
-            want = oracle.widen(inputs.f32_to_bf16_bits(want.astype(np.float32)))
-        try:
-            pl = cnn.plan_tiles(cnn.problem(*dims), MODES[mode], cnn.K_SPLITC, 32, 64, 128)
-        except cnn.CnnError:
-            assert dims[4] > 64  # the channel-slice slab itself
-            continue
-        assert pl.kc == 1 and pl.ws_bytes == 0
-        say(f"[small] direct slices dims={dims} mode={mode} v{pl.variant}")
-        assert np.array_equal(run(In, Ker, 1, 1, mode, plan=pl), want)
+@pytest.mark.parametrize("lds", [160, 128])
+def test_direct_slices(mode, lds):
+    """A direct channel-slice plan names the few-outputs kernel's launch (in
+    chunks of channels where the budget's LDS is smaller), and one that carries
+    the 32 x 64 tile of earlier versions still runs: both equal the oracle."""
+    dims = (1, 1024, 70, 7, 9, 3, 3, 1, 1)
+    prob, bud = cnn.problem(*dims), cnn.budget(lds_bytes=lds * 1024)
+    In, Ker = inputs.make_arrays(*dims, "bf16", seed_in=3, seed_ker=4, in_dist=("int", -2, 2),
+                                 ker_dist=("int", -2, 2))
+    want = oracle.conv(In, Ker, 1, 1)
+    if mode == "bf16_obf16":
+        want = oracle.widen(inputs.f32_to_bf16_bits(want.astype(np.float32)))
+    pl = cnn.plan_tiles(prob, MODES[mode], cnn.K_SPLITC, 32, 64, 128, bud)
+    assert pl.tk in (8, 16) and (pl.tc < dims[1]) == (lds < 160) and pl.lds_bytes <= lds * 1024
+    # the 32 x 64 tile: slab and grid of the other channel-slice plans, 128 channels a stage
+    old = cnn.Plan.from_buffer_copy(pl)
+    ref = cnn.plan_tiles(prob, MODES[mode], cnn.K_SPLITC, 32, 64, 64, bud)
+    old.tk, old.tp, old.tc, old.slab_rows, old.grid = 32, 64, 128, ref.slab_rows, ref.grid
+    old.lds_bytes = 16 * (9 * 16 * 33 + ref.slab_rows * 11 * 17)
+    for p in (pl, old):
+        say(f"[small] direct slices mode={mode} v{p.variant} tk={p.tk} tc={p.tc} lds={p.lds_bytes}")
+        assert np.array_equal(run(In, Ker, 1, 1, mode, plan=p), want)
