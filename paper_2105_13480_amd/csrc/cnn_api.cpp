@@ -142,15 +142,17 @@ const VariantS* find_variant_s(int id) {
 }
 
 // Geometry a few-channel plan must carry (the kernel sizes LDS from it).
-bool smallc_geometry_ok(const VariantS& v, const cnn_plan_t& pl) {
+// turn: its LDS is that of the 16-byte stores' turn.
+bool smallc_geometry_ok(const VariantS& v, const cnn_plan_t& pl, bool* turn) {
   const cnn_problem& p = pl.prob;
   if (p.Ns > 8 || (p.Nc * p.Nr + 1) / 2 > v.ks || pl.tp < 1 || pl.tp > v.tp ||
       !smallc_stencil_ok(v, p) || !ranges_ok_smallc(v, p, pl.dtype))
     return false;
   const int64_t S = slab_rows_max(p, pl.tp);
   const int64_t grid = ((p.Nb * p.Nw * p.Nh + pl.tp - 1) / pl.tp) * ((p.Nk + v.tk - 1) / v.tk);
-  return pl.slab_rows == S && pl.grid == grid && pl.lds_bytes == smallc_lds_bytes(v, p, S) &&
-         pl.lds_bytes <= 160 * 1024;
+  *turn = pl.dtype == CNN_BF16_OBF16 && pl.lds_bytes == smallc_lds_bytes(v, p, S, true);
+  return pl.slab_rows == S && pl.grid == grid &&
+         (*turn || pl.lds_bytes == smallc_lds_bytes(v, p, S, false)) && pl.lds_bytes <= 160 * 1024;
 }
 
 const VariantR* find_variant_r(int id) {
@@ -388,10 +390,11 @@ int run_plan(const void* In, const void* Ker, void* Out, const cnn_plan_t& pl, h
                  : launch_splitc(*v, In, Ker, Out, ws, a, pl.lds_bytes, pl.kc, pl.dtype, st);
   } else if (pl.kernel == CNN_K_SMALLC) {
     const VariantS* vs = find_variant_s(pl.variant);
-    if (!vs || vs->dtype != pl.dtype || vs->tk != pl.tk || !smallc_geometry_ok(*vs, pl))
+    bool turn = false;
+    if (!vs || vs->dtype != pl.dtype || vs->tk != pl.tk || !smallc_geometry_ok(*vs, pl, &turn))
       return fail(CNN_E_PLAN, "plan names no matching kernel instantiation (variant %d)", pl.variant);
     if (dry) return CNN_OK;
-    e = launch_smallc(*vs, In, Ker, Out, a, pl.lds_bytes, st);
+    e = launch_smallc(*vs, In, Ker, Out, a, pl.lds_bytes, turn, st);
   } else if (const Variant4* v4 = find_variant4(pl.variant)) {
     if (pl.kernel != CNN_K_IGEMM_WIDE || v4->dtype != pl.dtype || v4->tk != pl.tk ||
         v4->tp != pl.tp || v4->tc != pl.tc || pl.ws_bytes != igemm4_ws_bytes(*v4, pl.prob))

@@ -253,11 +253,14 @@ static bool eval_smallc(const cnn_problem& p, int dtype, const VariantS& v, cons
   if (p.Ns > 8 || (p.Nc * p.Nr + 1) / 2 > v.ks || !smallc_stencil_ok(v, p) ||
       !ranges_ok_smallc(v, p, dtype))
     return false;
-  const int64_t lds_full = smallc_lds_bytes(v, p, slab_rows_max(p, v.tp));
+  const int64_t lds_full = smallc_lds_bytes(v, p, slab_rows_max(p, v.tp), false);
   const int64_t occ = std::max<int64_t>(1, std::min<int64_t>(bud.wg_per_cu, bud.lds_bytes / lds_full));
   const int64_t tp = balanced_tp(p, v.tp, v.tk, bud.cus * occ, 1);
   const int64_t S = slab_rows_max(p, tp);
-  const int64_t lds = smallc_lds_bytes(v, p, S);
+  // (bf16 Out turned in LDS where that leaves as many workgroups on a CU)
+  int64_t lds = smallc_lds_bytes(v, p, S, true);
+  if (dtype != CNN_BF16_OBF16 || lds > std::min<int64_t>(80 * 1024, bud.lds_bytes / occ))
+    lds = smallc_lds_bytes(v, p, S, false);
   // one stage holds every channel (tc = Nc)
   return eval_tiling(p, dtype, v.id, v.tk, tp, p.Nc, v.acc, S, lds, 0, bud, plan);
 }

@@ -111,9 +111,10 @@ struct VariantS {
 };
 const VariantS* variants_smallc(int* count);
 bool smallc_stencil_ok(const VariantS& v, const cnn_problem& p);  // the problem fits a fixed stencil
-int64_t smallc_lds_bytes(const VariantS& v, const cnn_problem& p, int64_t slab_rows);
+// Its LDS, without or with the turn of bf16 Out to 16-byte stores.
+int64_t smallc_lds_bytes(const VariantS& v, const cnn_problem& p, int64_t slab_rows, bool turn);
 hipError_t launch_smallc(const VariantS& v, const void* In, const void* Ker, void* Out,
-                         const ConvArgs& a, int64_t lds_bytes, hipStream_t stream);
+                         const ConvArgs& a, int64_t lds_bytes, bool turn, hipStream_t stream);
 
 // A row-streaming instantiation (bf16, stride 1, fixed stencil): tk = 64,
 // tiles of whole output rows, Ker resident.

@@ -63,8 +63,8 @@ __device__ __forceinline__ uint32_t pk2_bf16(float x, float y) {
 // STG (bf16 Out): each wave turns its blocks through LDS of its own, so that a
 // lane stores 16 bytes of consecutive outputs of each of two features instead
 // of two bytes at a time (3-channel 7x7 stride-2 layer, batch 64, bf16 Out: 47.6 ->
-// 43.2 us); not where that LDS would cost
-// the second workgroup of a CU.
+// 43.2 us); not where that LDS, which the plan counts, would cost the second
+// workgroup of a CU.
 template <typename TO, int NB, int KS, bool SH2, bool STG, int FC = 0, int FR = 0, int FS = 0,
           int FST = 0>
 __global__ __launch_bounds__(256, 2) void conv_smallc(const bf16_t* __restrict__ In,
@@ -409,27 +409,25 @@ const VariantS* variants_smallc(int* count) {
   return kVariantsS;
 }
 
-int64_t smallc_lds_bytes(const VariantS& v, const cnn_problem& p, int64_t slab_rows) {
+// (turn: with the store turn's 16 pairs of features x tp outputs)
+int64_t smallc_lds_bytes(const VariantS& v, const cnn_problem& p, int64_t slab_rows, bool turn) {
   const int64_t Ny = p.sh * (p.Nh - 1) + p.Ns;
-  return (int64_t)v.ks * 2 * v.tk * 16 + p.Nc * slab_rows * ((Ny + 15) & ~(int64_t)7) * 2;
+  return (int64_t)v.ks * 2 * v.tk * 16 + p.Nc * slab_rows * ((Ny + 15) & ~(int64_t)7) * 2 +
+         (turn ? 16 * 4 * (int64_t)v.tp : 0);
 }
 
 template <int DT, int NB, int KS, int FC, int FR, int FS, int FST>
 static hipError_t launch_s(const void* In, const void* Ker, void* Out, const ConvArgs& a,
-                           int64_t lds, hipStream_t stream) {
+                           int64_t lds, bool turn, hipStream_t stream) {
   typedef typename std::conditional<DT == CNN_BF16, float, bf16_t>::type TO;
   auto kern = FST ? conv_smallc<TO, NB, KS, FST == 2, false, FC, FR, FS, FST>
                   : a.sh == 2 ? conv_smallc<TO, NB, KS, true, false>
                               : conv_smallc<TO, NB, KS, false, false>;
-  if constexpr (DT == CNN_BF16_OBF16) {
-    const int64_t staged = (lds + 15) / 16 * 16 + 4 * 16 * NB * 32 * 4;
-    if (staged <= 80 * 1024) {
-      lds = staged;
+  if constexpr (DT == CNN_BF16_OBF16)
+    if (turn)
       kern = FST ? conv_smallc<TO, NB, KS, FST == 2, true, FC, FR, FS, FST>
                  : a.sh == 2 ? conv_smallc<TO, NB, KS, true, true>
                              : conv_smallc<TO, NB, KS, false, true>;
-    }
-  }
   {
     const hipError_t e = allow_max_lds((const void*)kern);
     if (e != hipSuccess) return e;
@@ -457,11 +455,11 @@ static hipError_t launch_s(const void* In, const void* Ker, void* Out, const Con
 }
 
 hipError_t launch_smallc(const VariantS& v, const void* In, const void* Ker, void* Out,
-                         const ConvArgs& a, int64_t lds_bytes, hipStream_t stream) {
+                         const ConvArgs& a, int64_t lds_bytes, bool turn, hipStream_t stream) {
   switch (v.id) {
 #define CNN_CASES(id, dt, nb, ks, fc, fr, fs, fst) \
   case id:                                        \
-    return launch_s<dt, nb, ks, fc, fr, fs, fst>(In, Ker, Out, a, lds_bytes, stream);
+    return launch_s<dt, nb, ks, fc, fr, fs, fst>(In, Ker, Out, a, lds_bytes, turn, stream);
     CNN_SMALLC_VARIANTS(CNN_CASES)
 #undef CNN_CASES
     default:

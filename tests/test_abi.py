@@ -464,6 +464,29 @@ def test_direct_slice_plans_describe_their_launch(dtype):
     assert (far.variant, far.tk, far.tp, far.tc) == (2509 + dtype, 32, 64, 128)
 
 
+def test_smallc_plans_count_the_store_turns_lds():
+    """The few-channel kernel's bf16-Out plans hold the LDS that turns Out to
+    16-byte stores (64 bytes an output of the largest tile beside the fp32-Out
+    plan's), where two workgroups still share a CU and the budget allows it."""
+    p = cnn.problem(64, 3, 64, 112, 112, 7, 7, 2, 2)
+    tile = {v.variant: int(v.tp) for v in cnn.variants()}
+    for lds in (160 * 1024, 100 * 1024):
+        def plans(dt):
+            return {(c.variant % 100, int(c.tp)): c for c in
+                    cnn.plan_candidates(p, dt, cnn.budget(lds_bytes=lds)) if c.kernel == cnn.K_SMALLC}
+        f, b = plans(cnn.CNN_BF16), plans(cnn.CNN_BF16_OBF16)
+        assert f and f.keys() == b.keys()
+        turned = 0
+        for k in f:
+            turn = 64 * tile[b[k].variant]
+            both = f[k].lds_bytes + turn
+            occ = 2 if 2 * f[k].lds_bytes <= lds else 1
+            want = turn if both <= min(80 * 1024, lds // occ) else 0
+            assert b[k].lds_bytes == f[k].lds_bytes + want, k
+            turned += want > 0
+        assert (turned > 0) == (lds == 160 * 1024)
+
+
 def test_workspace_plans_need_the_workspace_form():
     """cnn_fwd_plan never allocates: a plan that needs a workspace is
     refused before any HIP call; cnn_fwd_plan_ws checks the workspace."""

@@ -69,6 +69,23 @@ def test_every_igemm_variant_exact_integers(case):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("lds", [160, 100])
+def test_smallc_bf16_out_with_and_without_the_turn(lds):
+    """bf16 Out of the few-channel kernel, stored through LDS and (a budget
+    without that LDS) two bytes at a time: the same bits, the oracle's."""
+    dims = (2, 3, 64, 40, 38, 7, 7, 2, 2)
+    In, Ker = _arrays(dims, "bf16", seed=78, dist=("int", -2, 2), kdist=("int", -2, 2))
+    want = oracle.conv(In, Ker, dims[7], dims[8])
+    want = inputs.bf16_bits_to_f32(inputs.f32_to_bf16_bits(want.astype(np.float32))).astype(np.float64)
+    plans = [c for c in cnn.plan_candidates(cnn.problem(*dims), cnn.CNN_BF16_OBF16,
+                                            cnn.budget(lds_bytes=lds * 1024))
+             if c.kernel == cnn.K_SMALLC]
+    assert plans
+    for pl in plans:
+        say(f"[parity] smallc v{pl.variant} tp={pl.tp} lds={pl.lds_bytes} of {lds} KiB")
+        assert np.array_equal(run(In, Ker, dims[7], dims[8], "bf16_obf16", plan=pl), want)
+
+
 @pytest.mark.parametrize("mode", ["bf16", "bf16_obf16"])
 def test_smallc_runs_of_tiles_exact(mode):
     """The few-channel kernel walks a run of tiles per workgroup (two
