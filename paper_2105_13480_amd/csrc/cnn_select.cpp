@@ -745,35 +745,36 @@ void hbm_terms(const cnn_plan_t& pl, int64_t xcds, int64_t l2, double terms[3]) 
     const int64_t cnt = q + (x < rem ? 1 : 0);
     if (cnt == 0) continue;
     const int64_t t0 = x * q + std::min(x, rem), t1 = t0 + cnt;
-    // input rows read: output row (b, w) reads rows b*Nx + sw*w .. + Nr - 1;
-    // the output rows are visited in increasing order, so a running end
-    // counts each row once.  Rows between strided reads are not read, but
-    // a gap shorter than a 128-byte line shares its lines with the rows
-    // around it, which HBM delivers whole: such gaps count as read.
+    // input rows read: output row (b, w) reads rows b*Nx + sw*w .. + Nr - 1.
+    // A run's tiles are consecutive outputs, so its output rows are, and each
+    // adds sw rows to the row before it in its image (Nr where the stride
+    // leaves rows out).  Rows between strided reads are not read, but a gap
+    // shorter than a 128-byte line shares its lines with the rows around it,
+    // which HBM delivers whole: such gaps count as read.
     const int64_t gap_max = (int64_t)((128.0 - 1.0) / (e_in * (double)Ny));  // rows
-    int64_t rows = 0, end = -1, max_slab = 0;
-    for (int64_t pt = t0 / n_k; pt <= (t1 - 1) / n_k; ++pt) {
-      const int64_t f = pt * tp, last = std::min(f + tp, npix) - 1;
-      const int64_t r0 = f / p.Nh, r1 = last / p.Nh;  // flattened (b, w) output rows
-      int64_t b = r0 / p.Nw, w = r0 % p.Nw;
-      max_slab = std::max(max_slab, p.sw * (r1 - r0) + p.Nr + (r1 / p.Nw - b) * (p.Nr - p.sw));
-      for (int64_t r = r0; r <= r1; ++r, ++w) {
-        if (w == p.Nw) w = 0, ++b;
-        const int64_t g0 = b * Nx + p.sw * w, g1 = g0 + p.Nr;
-        const int64_t from = (end >= 0 && g0 > end && g0 - end <= gap_max) ? end : std::max(g0, end);
-        if (g1 > from) rows += g1 - from;
-        end = std::max(end, g1);
-      }
+    const int64_t pa = t0 / n_k, pz = (t1 - 1) / n_k;
+    const int64_t ra = pa * tp / p.Nh, rz = (std::min((pz + 1) * tp, npix) - 1) / p.Nh;
+    const int64_t images = rz / p.Nw - ra / p.Nw + 1;
+    const int64_t step = p.sw <= p.Nr || p.sw - p.Nr <= gap_max ? p.sw : p.Nr;
+    in_b += (double)(images * p.Nr + (rz - ra + 1 - images) * step) * row_bytes;
+    // Ker tiles met: each once, or one for every tile (the last may be smaller)
+    const int64_t last = t1 / n_k - t0 / n_k;  // tiles of the last k tile
+    const double full = ker_bytes(0), less = full - ker_bytes(n_k - 1);
+    const double set = cnt >= n_k ? n_k * full - less : cnt * full - (last ? less : 0.0);
+    const double per_tile = cnt * full - last * less;
+    // the largest slab, walked only where it decides
+    auto slab = [&](int64_t pt) {
+      const int64_t r0 = pt * tp / p.Nh, r1 = (std::min((pt + 1) * tp, npix) - 1) / p.Nh;
+      return p.sw * (r1 - r0) + p.Nr + (r1 / p.Nw - r0 / p.Nw) * (p.Nr - p.sw);
+    };
+    auto fits = [&](int64_t rows) { return set + (double)rows * row_bytes <= (double)l2; };
+    const int64_t dr = (std::min(tp, npix) + p.Nh - 2) / p.Nh;  // output rows of a tile, less one
+    bool once = fits(p.sw * dr + p.Nr + (dr + p.Nw - 1) / p.Nw * std::max<int64_t>(0, p.Nr - p.sw));
+    if (!once) {
+      once = true;
+      for (int64_t pt = pa; once && pt <= pz; ++pt) once = fits(slab(pt));
     }
-    in_b += (double)rows * row_bytes;
-    double set = 0.0, per_tile = 0.0;
-    for (int64_t kt = 0; kt < n_k; ++kt) {  // k tiles the run meets
-      bool met = cnt >= n_k;
-      for (int64_t t = t0; !met && t < t1; ++t) met = t % n_k == kt;
-      if (met) set += ker_bytes(kt);
-    }
-    for (int64_t t = t0; t < t1; ++t) per_tile += ker_bytes(t % n_k);
-    ker_b += set + (double)max_slab * row_bytes <= (double)l2 ? set : per_tile;
+    ker_b += once ? set : per_tile;
   }
   const double out = (double)npix * (double)p.Nk;
   terms[0] = e_out * out +
