@@ -578,8 +578,15 @@ static FamilyCost family_cost(int kernel, int variant, int dtype) {
       int n = 0;
       const VariantG* vg = variants_gemm1(&n);
       for (int i = 0; i < n; ++i)
-        if (vg[i].id == variant && vg[i].s2 == 2) return {0.99, 4.21, 0.50, 77.2};  // DMA ring
-      return {0.35, 4.19, 0.54, 29.5};
+        if (vg[i].id == variant && vg[i].s2 == 2)
+          return {0.99, 4.21, 0.50, 77.2};  // DMA ring
+        else if (vg[i].id == variant && vg[i].s2 == 0)
+          // a stage of 256 features costs twice that of 128 (272 -> 284 at
+          // 26x26, batch 20, bf16 Out: 18.8 and 12.8 us, which one cost row
+          // for both took for equal)
+          return vg[i].tk == 256 ? FamilyCost{0.48, 4.18, 1.72, 94.6}
+                                 : FamilyCost{0.35, 2.74, 0.94, 75.6};
+      return {0.35, 4.19, 0.54, 29.5};  // stride 2
     }
     case CNN_K_SMALLC: {
       int n = 0;

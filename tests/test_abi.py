@@ -487,6 +487,17 @@ def test_smallc_plans_count_the_store_turns_lds():
         assert (turned > 0) == (lds == 160 * 1024)
 
 
+@pytest.mark.parametrize("dims", [(20, 272, 284, 26, 26, 1, 1, 1, 1), (40, 224, 112, 22, 22, 1, 1, 1, 1)])
+def test_gemm1_stage_costs_by_tile(dims):
+    """The 1x1 kernel's 256-feature tiles are not priced as its 128-feature
+    ones, half of whose stage they cost: 18.8 and 16.9 us measured where those
+    take 12.8 and 11.2."""
+    p = cnn.problem(*dims)
+    t = {c.variant: c.model_us for c in cnn.plan_candidates(p, cnn.CNN_BF16_OBF16, cnn.budget())}
+    assert t[1801] < 0.9 * t[1800]
+    assert cnn.plan_tiles(p, cnn.CNN_BF16_OBF16, cnn.K_AUTO_NO_WORKSPACE, bud=cnn.budget()).variant == 1801
+
+
 def test_workspace_plans_need_the_workspace_form():
     """cnn_fwd_plan never allocates: a plan that needs a workspace is
     refused before any HIP call; cnn_fwd_plan_ws checks the workspace."""
