@@ -480,25 +480,27 @@ const VariantM* small_variant(const cnn_plan_t& pl) {
   return nullptr;
 }
 
-// Its time: rounds of as many workgroups as LDS and 2048 threads per CU allow,
-// each a latency, its Ker and In bytes at what a CU keeps outstanding, and its
-// gathers (wave reads); fitted like the tile kernel's, to 636 launches.
+// Its time: rounds of as many workgroups as LDS and the waves that its registers
+// allow, each a latency, its Ker and In bytes at what a CU keeps outstanding, and
+// its gathers (wave reads); fitted like the tile kernel's, to 636 launches.  Ker
+// rows at odd elements cost eight times: every 16-byte load crosses words (295
+// launches with K from 9 to 18000; batch-1 3x3 layers of 871 and 1353 channels 29
+// and 44 us, 13 and 17 by even rows' sum).
 static double small_us(const cnn_problem& p, int dtype, const VariantM& v, const SmallShape& s,
                        const cnn_budget& bud) {
   const double es = in_bytes(dtype), K = (double)(p.Nc * p.Nr * p.Ns);
-  const double ker_kb = (double)v.tk * K * es / 1000, in_kb = (double)(p.Nc * s.LP) * es / 1000;
+  const double odd = dtype != CNN_F32 && (p.Nc * p.Nr * p.Ns) % 2 ? 7.0 : 1.0;
+  const double ker_kb = (double)v.tk * K * es / 1000 * odd, in_kb = (double)(p.Nc * s.LP) * es / 1000;
   const double gathers = std::ceil(K / (dtype == CNN_F32 ? 16 : 32)) * (double)(v.tp / 16) *
                          (dtype == CNN_F32 ? 4 : 8);
-  const int64_t occ = std::max<int64_t>(1, std::min<int64_t>(bud.lds_bytes / s.lds, 32 / s.waves));
+  const int64_t occ =
+      std::max<int64_t>(1, std::min<int64_t>(bud.lds_bytes / s.lds, v.simd / (s.waves / 4)));
   const int64_t n = ceil_div(s.grid, bud.cus);
   auto round = [&](double k) {
-    return 2.52 + k * (in_kb * 0.0334 + ker_kb * 0.0084 + gathers * 0.0020);
+    return 2.52 + k * ((odd > 1.0 ? 0.9 : 0.0) + in_kb * 0.0334 + ker_kb * 0.0084 +
+                       gathers * 0.0020);
   };
-  // Ker rows at odd elements: every 16-byte load crosses words (batch-1 3x3
-  // layers of 871, 1093 and 1353 channels: 29, 34 and 44 us where this sum says
-  // 13, 16 and 17)
-  const double odd = dtype != CNN_F32 && (p.Nc * p.Nr * p.Ns) % 2 ? 2.2 : 1.0;
-  return 1.75 + odd * (double)(n / occ) * round((double)occ) + odd * (n % occ ? round((double)(n % occ)) : 0.0);
+  return 1.75 + (double)(n / occ) * round((double)occ) + (n % occ ? round((double)(n % occ)) : 0.0);
 }
 
 const VariantM* small_direct(const cnn_problem& p, int dtype, const cnn_budget& bud,

@@ -215,6 +215,7 @@ struct VariantM {
   int32_t tk;
   int64_t tp;
   int32_t acc;
+  int32_t simd;  // waves its registers allow on a SIMD
 };
 const VariantM* variants_small(int* count);
 struct SmallShape {

@@ -250,22 +250,22 @@ __global__ __launch_bounds__(1024) void conv_small(const TI* __restrict__ In,
 }
 
 // ---- instantiation table ----------------------------------------------------
-// (id, dtype, PB, KF): tk = KF, tp = 16 PB.
-#define CNN_SMALL_VARIANTS(X)    \
-  X(3300, CNN_F32, 1, 16)        \
-  X(3301, CNN_F32, 2, 16)        \
-  X(3302, CNN_F32, 1, 8)         \
-  X(3310, CNN_BF16, 1, 16)       \
-  X(3311, CNN_BF16, 2, 16)       \
-  X(3312, CNN_BF16, 4, 16)       \
-  X(3313, CNN_BF16, 1, 8)        \
-  X(3320, CNN_BF16_OBF16, 1, 16) \
-  X(3321, CNN_BF16_OBF16, 2, 16) \
-  X(3322, CNN_BF16_OBF16, 4, 16) \
-  X(3323, CNN_BF16_OBF16, 1, 8)
+// (id, dtype, PB, KF, waves on a SIMD as its registers allow): tk = KF, tp = 16 PB.
+#define CNN_SMALL_VARIANTS(X)       \
+  X(3300, CNN_F32, 1, 16, 7)        \
+  X(3301, CNN_F32, 2, 16, 6)        \
+  X(3302, CNN_F32, 1, 8, 7)         \
+  X(3310, CNN_BF16, 1, 16, 5)       \
+  X(3311, CNN_BF16, 2, 16, 4)       \
+  X(3312, CNN_BF16, 4, 16, 4)       \
+  X(3313, CNN_BF16, 1, 8, 5)        \
+  X(3320, CNN_BF16_OBF16, 1, 16, 5) \
+  X(3321, CNN_BF16_OBF16, 2, 16, 4) \
+  X(3322, CNN_BF16_OBF16, 4, 16, 4) \
+  X(3323, CNN_BF16_OBF16, 1, 8, 5)
 
 static const VariantM kVariantsM[] = {
-#define CNN_ROWM(id, dt, pb, kf) {id, dt, kf, 16 * (pb), 4 * (pb)},
+#define CNN_ROWM(id, dt, pb, kf, simd) {id, dt, kf, 16 * (pb), 4 * (pb), simd},
     CNN_SMALL_VARIANTS(CNN_ROWM)
 #undef CNN_ROWM
 };
@@ -349,8 +349,8 @@ hipError_t launch_small(const VariantM& v, const void* In, const void* Ker, void
   t.rs = make_fastdiv((uint32_t)(a.Nr * a.Ns));
   t.ns = make_fastdiv((uint32_t)a.Ns);
   switch (v.id) {
-#define CNN_CASEM(id, dt, pb, kf) \
-  case id:                        \
+#define CNN_CASEM(id, dt, pb, kf, simd) \
+  case id:                              \
     return launch_m<dt, pb, kf>(In, Ker, Out, a, t, s, stream);
     CNN_SMALL_VARIANTS(CNN_CASEM)
 #undef CNN_CASEM

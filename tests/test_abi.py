@@ -498,6 +498,17 @@ def test_gemm1_stage_costs_by_tile(dims):
     assert cnn.plan_tiles(p, cnn.CNN_BF16_OBF16, cnn.K_AUTO_NO_WORKSPACE, bud=cnn.budget()).variant == 1801
 
 
+@pytest.mark.parametrize("dims", [(7, 335, 16, 87, 9, 1, 1, 2, 2), (1, 181, 158, 8, 25, 3, 3, 2, 2),
+                                  (1, 825, 304, 21, 21, 3, 3, 1, 1)])
+@pytest.mark.parametrize("dtype", [1, 2])
+def test_few_outputs_price_odd_rows_by_their_bytes(dims, dtype):
+    """Ker rows at odd elements make the few-outputs kernel's Ker loads dearer,
+    not all of its work: it is the plan of these layers (9.1, 11.9 and 39 us
+    where the tile kernel takes 20.8, 21 and 75)."""
+    pl = cnn.plan_tiles(cnn.problem(*dims), dtype, cnn.K_AUTO_NO_WORKSPACE, bud=cnn.budget())
+    assert pl.kernel == cnn.K_IGEMM and 3300 <= pl.variant < 3400
+
+
 def test_workspace_plans_need_the_workspace_form():
     """cnn_fwd_plan never allocates: a plan that needs a workspace is
     refused before any HIP call; cnn_fwd_plan_ws checks the workspace."""
