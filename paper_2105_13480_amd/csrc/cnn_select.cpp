@@ -952,6 +952,9 @@ int enumerate_plans(const cnn_problem& p, int dtype, const cnn_budget& bud, cnn_
     // are padding: 64 features at 112x112, batch 8, of 4 channels 14.6 us
     // against 10.8 by the fp32 units' tiles 1x1, 21.1 against 19.7 3x3)
     if (dtype == CNN_F32 && 2 * p.Nc < vtl[i].tc) continue;
+    // (its registers spill, 190 bytes a lane: 0.6 of the speed that the model
+    // gives it on 87 layers, never the best)
+    if (vtl[i].nr == 0 && vtl[i].tk == 128 && p.Ns == 1 && p.sh == 2) continue;
     if (eval_tile(p, dtype, vtl[i], 0, bud, &cand)) add(cand, CNN_K_IGEMM);
   }
   int ncs = 0;

@@ -905,7 +905,8 @@ static hipError_t launch_t(const void* In, const void* Ker, void* Out, const Con
   if (form == kWide1) kern = conv_tile<TI, TO, WM, WN, MB, NB, KS, NR, NS, MAXP, KCH, OCC, kWide1>;
   if constexpr (NS != 1)
     if (form == kWide2) kern = conv_tile<TI, TO, WM, WN, MB, NB, KS, NR, NS, MAXP, KCH, OCC, kWide2>;
-  if constexpr (NS <= 1)  // 1 wide, or any
+  // 1 wide, or any; not with 128 features on four waves (tile_geometry)
+  if constexpr (NS <= 1 && !(NR == 1 && WM * MB == 4 && WM * WN == 4))
     if (form == kGather2)
       kern = conv_tile<TI, TO, WM, WN, MB, NB, KS, NR, NS, MAXP, KCH, OCC, kGather2>;
   if (!kern) return hipErrorInvalidValue;
