@@ -948,10 +948,10 @@ int enumerate_plans(const cnn_problem& p, int dtype, const cnn_budget& bud, cnn_
   const VariantT* vtl = variants_tile(&ntl);
   for (int i = 0; i < ntl; ++i) {
     if (vtl[i].dtype != dtype) continue;
-    // (fp32: six products a channel, so not where most of a stage's channels
-    // are padding: 64 features at 112x112, batch 8, of 4 channels 14.6 us
-    // against 10.8 by the fp32 units' tiles 1x1, 21.1 against 19.7 3x3)
-    if (dtype == CNN_F32 && 2 * p.Nc < vtl[i].tc) continue;
+    // (fp32 sums of fewer than eight products are computed on the fp32 units, in a
+    // second pass: 64 features at 112x112, batch 8, of 4 channels 1x1 22 us against
+    // 10.8 by the fp32 units' own tiles)
+    if (dtype == CNN_F32 && p.Nc * p.Nr * p.Ns < 8) continue;
     // (its registers spill, 190 bytes a lane: 0.6 of the speed that the model
     // gives it on 87 layers, never the best)
     if (vtl[i].nr == 0 && vtl[i].tk == 128 && p.Ns == 1 && p.sh == 2) continue;

@@ -151,13 +151,22 @@ struct SplitRange {
   __device__ __forceinline__ bool small() const { return lo < (25u << 24) - 1u; }
 };
 
+// Workgroups per CU that the registers of an instantiation leave room for.  fp32
+// on four waves: two, not one, within 256 registers a lane, at 19 spilled ones for
+// runtime stencils (16 -> 32 features 1x1 at 94x94, batch 22: 24.6 -> 16.1 us) and
+// without accumulators to be copied out for 3x3 (16 -> 129 at 60x60, batch 6: 17.5
+// -> 16.4); not the gathered form, which would spill more.
+template <typename TI, int NW, int OCC, int FORM> constexpr int tile_occ() {
+  return std::is_same<TI, float>::value && NW == 4 && FORM != kGather2 ? 2 : OCC;
+}
+
 // TI: bf16_t or float; TO: the Out type.  WM x WN = 4 waves, MB x NB blocks
 // of 32 features x 32 outputs per wave, KS K-steps of 16 channels per stage,
 // NR x NS the stencil (0: any), MAXP In items and KCH Ker items per
 // thread, OCC workgroups per CU.  FORM: how columns are staged (kPairs ...).
 template <typename TI, typename TO, int WM, int WN, int MB, int NB, int KS, int NR, int NS,
           int MAXP, int KCH, int OCC, int FORM>
-__global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(const TI* __restrict__ In,
+__global__ __launch_bounds__(64 * WM * WN, (tile_occ<TI, WM * WN, OCC, FORM>() * WM * WN / 4)) void conv_tile(const TI* __restrict__ In,
                                                       const TI* __restrict__ Ker,
                                                       TO* __restrict__ Out, ConvArgs a,
                                                       TileGeo t) {
@@ -674,45 +683,46 @@ __global__ __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4) void conv_tile(con
     // (what is below the least normal number), a sum of K products less than
     // K 2^-124 top, top the largest value: sums of 2^26 times that keep fp32's
     // accuracy, so one small weight or input among ordinary ones costs nothing.
-    // (The buffers are free: the votes there.)
-    uint32_t* vote = reinterpret_cast<uint32_t*>(smem);  // [0] recompute, [1] small values, [2] top
-    float nan = 0.f;  // 0 times every sum: NaN if one is not finite
+    // The sums are looked at only where a value is small, or so large that K
+    // products of two such may overflow.
+    const int K = a.Nc * RS;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          acc[mb][nb][j] += low[mb][nb][j];
-          nan = __builtin_fmaf(acc[mb][nb][j], 0.f, nan);
-        }
+        for (int j = 0; j < 16; ++j) acc[mb][nb][j] += low[mb][nb][j];
+    // (the buffers are free: the votes there)
+    uint32_t* vote = reinterpret_cast<uint32_t*>(smem);  // small values, large ones, the largest, again
     __syncthreads();
-    if (tid < 3) vote[tid] = 0u;
+    if (tid < 4) vote[tid] = 0u;
     __syncthreads();
-    if (nan != 0.f || t.units) vote[0] = 1u;
-    if (range.small()) vote[1] = 1u;
+    if (range.small()) vote[0] = 1u;
+    if (range.hi >= (uint32_t)(126 + (126 - (32 - __builtin_clz(K))) / 2) << 24) vote[1] = 1u;
     __syncthreads();
-    bool again = vote[0] != 0u;
-    if (!again && vote[1]) {
-      atomicMax(&vote[2], range.hi >> 1);
-      float least = __builtin_inff();
+    bool again = t.units;
+    if (!again && (vote[0] | vote[1])) {
+      float least = __builtin_inff(), nan = 0.f;  // 0 times every sum: NaN if one is not finite
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-          for (int j = 0; j < 16; ++j) least = fminf(least, fabsf(acc[mb][nb][j]));
+          for (int j = 0; j < 16; ++j) {
+            least = fminf(least, fabsf(acc[mb][nb][j]));
+            nan = __builtin_fmaf(acc[mb][nb][j], 0.f, nan);
+          }
+      atomicMax(&vote[2], range.hi >> 1);
       __syncthreads();
-      const float bound = (float)(a.Nc * RS) * 0x1p-98f * __uint_as_float(vote[2]);
-      if (!(least >= bound)) vote[0] = 1u;
+      const float bound = vote[0] ? (float)K * 0x1p-98f * __uint_as_float(vote[2]) : 0.f;
+      if (nan != 0.f || !(least >= bound)) vote[3] = 1u;
       __syncthreads();
-      again = vote[0] != 0u;
+      again = vote[3] != 0u;
     }
     if (again) {
       // Straight from memory: of the flattened (c, r, s) index of a feature, a
       // lane's half takes four elements of every eight, 16 bytes of Ker and
       // four gathers of In, two such steps ahead of the products.
-      const int K = a.Nc * RS;
       const uint32_t kmax = (uint32_t)(a.Nk - 1);
       uint32_t ko[MB], io[NB];
 #pragma unroll

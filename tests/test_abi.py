@@ -509,6 +509,14 @@ def test_few_outputs_price_odd_rows_by_their_bytes(dims, dtype):
     assert pl.kernel == cnn.K_IGEMM and 3300 <= pl.variant < 3400
 
 
+@pytest.mark.parametrize("nc,r,tile", [(1, 1, False), (7, 1, False), (8, 1, True), (1, 3, True)])
+def test_fp32_tiles_from_eight_products_on(nc, r, tile):
+    """Sums of fewer than eight products, which the tile kernel's bf16 parts do
+    not give with fp32's accuracy, are left to the fp32 units' kernels."""
+    c = cnn.plan_candidates(cnn.problem(8, nc, 64, 112, 112, r, r, 1, 1), cnn.CNN_F32, cnn.budget())
+    assert any(3000 <= x.variant < 3300 for x in c) == tile
+
+
 def test_workspace_plans_need_the_workspace_form():
     """cnn_fwd_plan never allocates: a plan that needs a workspace is
     refused before any HIP call; cnn_fwd_plan_ws checks the workspace."""
