@@ -800,21 +800,23 @@ __global__ __launch_bounds__(64 * WM * WN, (tile_occ<TI, WM * WN, OCC, FORM>() *
       rsrc_t(Out + (int64_t)b0 * a.Nk * a.hw,
              (a.out_total - (int64_t)b0 * a.Nk * a.hw) * (int64_t)sizeof(TO));
   const int ch = lane % CPR, frow = lane / CPR;
-  uint32_t oo[OPC];  // byte offsets of the chunk's outputs, feature k0
+  // byte offsets of the chunk's outputs, feature k0; past every feature's end
+  // (the store is dropped) for those that are not, or that the neighbouring band
+  // stores
+  constexpr uint32_t kNone = 0x80000000u;
+  uint32_t oo[OPC];
   const int qlast = (wn * NB) * 32 + ch * OPC + OPC - 1;
-  uint32_t skip = 0u;  // (fp32) those that the neighbouring band stores, a bit each
 #pragma unroll
   for (int e = 0; e < OPC; ++e) {
     const int q = min(qlast - (OPC - 1) + e, nout - 1);
     const int i = fdiv(q, t.ctd);
-    if (F32 && q - i * cols < own) skip |= 1u << e;
     const int orow = row0 + i;
     const int b = fdiv(orow, t.nw);
     oo[e] = (uint32_t)((((int64_t)(b - b0) * a.Nk + k0) * a.hw + (int64_t)(orow - b * a.Nw) * a.Nh +
                         h0 + q - i * cols) * (int64_t)sizeof(TO));
+    if (qlast - (OPC - 1) + e >= nout || (F32 && q - i * cols < own)) oo[e] = kNone;
   }
-  const bool whole =
-      qlast < nout && !skip && oo[OPC - 1] - oo[0] == (OPC - 1) * sizeof(TO);
+  const bool whole = oo[OPC - 1] - oo[0] == (OPC - 1) * sizeof(TO);
   const uint32_t fbytes = (uint32_t)a.hw * (uint32_t)sizeof(TO);
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
@@ -859,14 +861,13 @@ __global__ __launch_bounds__(64 * WM * WN, (tile_occ<TI, WM * WN, OCC, FORM>() *
           __builtin_amdgcn_raw_buffer_store_b128(v[u], orr, oo[0] + fo, 0, 0);
         } else {
 #pragma unroll
-          for (int e = 0; e < OPC; ++e)
-            if (qlast - (OPC - 1) + e < nout && !(skip >> e & 1u)) {
-              if constexpr (O16)
-                __builtin_amdgcn_raw_buffer_store_b16(
-                    (uint16_t)(v[u][e >> 1] >> (16 * (e & 1))), orr, oo[e] + fo, 0, 0);
-              else
-                __builtin_amdgcn_raw_buffer_store_b32(v[u][e], orr, oo[e] + fo, 0, 0);
-            }
+          for (int e = 0; e < OPC; ++e) {
+            if constexpr (O16)
+              __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v[u][e >> 1] >> (16 * (e & 1))), orr,
+                                                    oo[e] + fo, 0, 0);
+            else
+              __builtin_amdgcn_raw_buffer_store_b32(v[u][e], orr, oo[e] + fo, 0, 0);
+          }
         }
       }
     }
