@@ -497,8 +497,9 @@ static double small_us(const cnn_problem& p, int dtype, const VariantM& v, const
       std::max<int64_t>(1, std::min<int64_t>(bud.lds_bytes / s.lds, v.simd / (s.waves / 4)));
   const int64_t n = ceil_div(s.grid, bud.cus);
   auto round = [&](double k) {
-    return 2.52 + k * ((odd > 1.0 ? 0.9 : 0.0) + in_kb * 0.0334 + ker_kb * 0.0084 +
-                       gathers * 0.0020);
+    return 2.52 + k * (dtype == CNN_F32
+                           ? in_kb * 0.0198 + ker_kb * 0.0090 + gathers * 0.0039
+                           : (odd > 1.0 ? 0.9 : 0.0) + in_kb * 0.0334 + ker_kb * 0.0084 + gathers * 0.0020);
   };
   return 1.75 + (double)(n / occ) * round((double)occ) + (n % occ ? round((double)(n % occ)) : 0.0);
 }
