@@ -483,9 +483,11 @@ const VariantM* small_variant(const cnn_plan_t& pl) {
 // Its time: rounds of as many workgroups as LDS and the waves that its registers
 // allow, each a latency, its Ker and In bytes at what a CU keeps outstanding, and
 // its gathers (wave reads); fitted like the tile kernel's, to 636 launches.  Ker
-// rows at odd elements cost eight times: every 16-byte load crosses words (295
-// launches with K from 9 to 18000; batch-1 3x3 layers of 871 and 1353 channels 29
-// and 44 us, 13 and 17 by even rows' sum).
+// rows at odd elements cost seven times and 0.9 us: every 16-byte load crosses
+// words (295 launches with K from 9 to 18000, spread 16 %; batch-1 3x3 layers of
+// 871 and 1353 channels 29 and 44 us, 13 and 17 by even rows' sum).  fp32 has
+// rates of its own (798 launches, spread 19 -> 16 %): cheaper bytes of In, which
+// it gathers as they are, and twice the reads for as many products.
 static double small_us(const cnn_problem& p, int dtype, const VariantM& v, const SmallShape& s,
                        const cnn_budget& bud) {
   const double es = in_bytes(dtype), K = (double)(p.Nc * p.Nr * p.Ns);

@@ -35,6 +35,10 @@ SHAPES = [
 ]
 
 
+# No instantiation fits: the Ker items of 49 fp32 taps a stage.
+NO_TILE = {("f32", (1, 9, 34, 8, 10, 7, 7, 2, 2))}
+
+
 def _ints(dims, mode, seed):
     return inputs.make_arrays(*dims, "f32" if mode == "f32" else "bf16", seed_in=seed,
                               seed_ker=seed + 1, in_dist=("int", -2, 2), ker_dist=("int", -2, 2))
@@ -46,7 +50,7 @@ def _tile_plans(dims, mode):
     seen, out = set(), []
     for cus in (256, 2):
         for c in cnn.plan_candidates(cnn.problem(*dims), MODES[mode], cnn.budget(cus=cus)):
-            if c.kernel == cnn.K_IGEMM and c.variant >= 3000 and (c.variant, c.kc) not in seen:
+            if c.kernel == cnn.K_IGEMM and 3000 <= c.variant < 3300 and (c.variant, c.kc) not in seen:
                 seen.add((c.variant, c.kc))
                 out.append(c)
     return out
@@ -82,7 +86,9 @@ def test_tile_exact_integers(dims, mode):
     if mode == "bf16_obf16":
         want = oracle.widen(inputs.f32_to_bf16_bits(want.astype(np.float32)))
     plans = _tile_plans(dims, mode)
-    assert plans or max(dims[5], dims[6]) > 5
+    if not plans:  # sums the selector leaves to the fp32 units: by their tilings
+        plans = _all_tile_plans(dims, mode)
+    assert plans or (mode, dims) in NO_TILE
     for pl in plans:
         say(f"[tile] dims={dims} mode={mode} v{pl.variant} rows={pl.kc} tp={pl.tp} grid={pl.grid}")
         got = run(In, Ker, dims[7], dims[8], mode, plan=pl)
@@ -143,21 +149,26 @@ def test_tile_f32_outside_the_split(dims, case):
         Ker = np.abs(Ker) * np.float32(1e25)
     elif case == "tiny":
         In *= np.float32(1e-34)
-    else:
+    else:  # the first image's outputs are a subnormal channel's alone
+        In[0, :3], In[0, 4:] = 0, 0
         In[0, 3] *= np.float32(1e-40)
     prob = cnn.problem(*dims)
     say(f"[tile] f32 {case} dims={dims}: direct kernel")
     ref = run(In, Ker, dims[7], dims[8], "f32", plan=cnn.plan_tiles(prob, cnn.CNN_F32, cnn.K_DIRECT))
-    scale = np.abs(ref[np.isfinite(ref)]).max(initial=0.0)
     assert case != "overflow" or np.isposinf(ref).all()
-    for pl in _tile_plans(dims, "f32"):
+    # each output against its own sum of |In Ker|, and the least number a product
+    scale = 1e-5 * oracle.conv(np.where(np.isfinite(In), np.abs(In), 0), np.abs(Ker), dims[7], dims[8])
+    scale += dims[1] * dims[5] * dims[6] * 2.0 ** -149
+    plans = _tile_plans(dims, "f32")
+    assert plans
+    for pl in plans:
         say(f"[tile] f32 {case} dims={dims} v{pl.variant} rows={pl.kc}")
         got = run(In, Ker, dims[7], dims[8], "f32", plan=pl)
         assert np.array_equal(np.isnan(got), np.isnan(ref)), pl.variant
         assert np.array_equal(np.isinf(got), np.isinf(ref)), pl.variant
         fine = np.isfinite(ref)
         assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
-        assert np.abs(got[fine] - ref[fine]).max(initial=0.0) <= 1e-5 * scale, pl.variant
+        assert (np.abs(got[fine] - ref[fine]) <= scale[fine]).all(), pl.variant
 
 
 @pytest.mark.parametrize("dims", [(2, 20, 40, 9, 13, 3, 3, 1, 1), (2, 33, 34, 6, 9, 1, 1, 2, 2),
@@ -248,9 +259,9 @@ def test_tile_f32_bands_store_what_they_own(dims):
                                  in_dist=("uniform", -1.0, 1.0), ker_dist=("he",))
     bad = In.copy()
     bad[0, 3, 1, -1] = np.inf  # read by the last output column alone
-    for pl in _tile_plans(dims, "f32"):
-        if pl.variant >= 3300 or Nh % (pl.tp // pl.kc) == 0:
-            continue
+    plans = [pl for pl in _tile_plans(dims, "f32") if Nh % (pl.tp // pl.kc)]
+    assert plans
+    for pl in plans:
         ct = pl.tp // pl.kc
         first = Nh // ct * ct  # the last band's own columns
         assert first < Nh - Ns
@@ -284,7 +295,11 @@ def test_tensors_at_odd_addresses(dims, mode):
         return view
 
     dIn, dKer = shifted(to_gpu(In)), shifted(to_gpu(Ker))
-    for pl in _tile_plans(dims, mode):
+    few = [c for c in cnn.plan_candidates(cnn.problem(*dims), MODES[mode])
+           if c.kernel == cnn.K_IGEMM and 3300 <= c.variant < 3400]
+    tiles = _tile_plans(dims, mode)
+    assert tiles and len(few) >= 3
+    for pl in tiles + few:
         dOut = shifted(out_tensor(Nb, Nk, Nw, Nh, mode))
         say(f"[tile] odd addresses dims={dims} mode={mode} v{pl.variant} rows={pl.kc}")
         cnn.fwd_plan(dIn, dKer, dOut, pl, dims[7], dims[8])
