@@ -817,6 +817,7 @@ __global__ __launch_bounds__(64 * WM * WN, (tile_occ<TI, WM * WN, OCC, FORM>() *
     if (qlast - (OPC - 1) + e >= nout || (F32 && q - i * cols < own)) oo[e] = kNone;
   }
   const bool whole = oo[OPC - 1] - oo[0] == (OPC - 1) * sizeof(TO);
+  const bool some = oo[0] != kNone || oo[OPC - 1] != kNone;
   const uint32_t fbytes = (uint32_t)a.hw * (uint32_t)sizeof(TO);
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
@@ -859,7 +860,7 @@ __global__ __launch_bounds__(64 * WM * WN, (tile_occ<TI, WM * WN, OCC, FORM>() *
         const uint32_t fo = (uint32_t)(kl + u) * fbytes;
         if (whole) {
           __builtin_amdgcn_raw_buffer_store_b128(v[u], orr, oo[0] + fo, 0, 0);
-        } else {
+        } else if (some) {
 #pragma unroll
           for (int e = 0; e < OPC; ++e) {
             if constexpr (O16)
