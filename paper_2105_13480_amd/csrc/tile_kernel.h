@@ -9,11 +9,11 @@
 // cut into ncol bands of ct columns, one workgroup each, so that the halo of
 // a wide image stays that of a two-dimensional tile.
 //
-// * In: per stage, 16-bit elements are loaded as dwords holding two
-//   neighbouring columns of one channel (any 2-byte alignment; the last pair
-//   of an odd row starts one column earlier, so no load leaves its row), 8
-//   channels per work item, transposed in registers (v_perm) into two
-//   16-byte [8 channels] vectors.  LDS holds [channel group][row][column],
+// * In: a work item is 16 bytes of a row (8 columns of bf16, 4 of fp32) of each
+//   of 8 channels, at any alignment of an element (h strides 1 and 2; the last
+//   item of a row ends with it, so no load leaves its row), or a pair of columns
+//   (larger strides, the narrowest bands), transposed in registers (v_perm) into
+//   16-byte [8 channels] vectors, one a column.  LDS holds [channel group][row][column],
 //   columns split by their residue modulo the h stride, so that a tap's
 //   operand is a run of consecutive vectors for any stride.  Rows and
 //   (1-wide stencils) columns that no output reads are not staged.
@@ -28,12 +28,12 @@
 //   i + 2 at once, so that a load has a whole stage to land and the matrix
 //   units do not wait for a staging phase; one barrier per stage.
 // * What bounds it: LDS bandwidth and vector instruction issue beside the
-//   products (64 -> 64 features at 224x224, 3x3, batch 8, bf16 Out: matrix
-//   units busy 31 % of the cycles, LDS 45 %, before the conflict-free Ker
-//   writes).  On that layer, from 96 us of the whole-row tiles (whose slab is
+//   products (64 -> 64 features at 224x224, 3x3, batch 8, bf16 Out: 41.8 us as one
+//   kernel, 44 a call of many; matrix units busy 44 % of the cycles, LDS 38 %).
+//   On that layer, kernel alone, from 96 us of the whole-row tiles (whose slab is
 //   2.2 times the outputs): 63 with this tile and dword loads, 54 with the
 //   staging between the products, 50 with 16-byte loads and Out through LDS,
-//   44 with Ker in channel pairs, 39 with two workgroups per CU.
+//   44 with Ker in channel pairs, 42 with two workgroups per CU.
 // * fp32 (CNN_F32): In and Ker values are split into three bf16 parts that
 //   sum to them exactly (truncation, then two roundings: 8 + 8 + 8 bits) and
 //   the six products of combined order up to 2^-16 are accumulated in fp32 by
