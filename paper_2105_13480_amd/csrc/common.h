@@ -27,6 +27,23 @@ template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float x) {
   return (bf16_t)(u >> 16);
 }
 
+// Two fp32 values as bf16 (round to nearest, ties to even), x in the low half.
+__device__ __forceinline__ uint32_t pk_bf16(float x, float y) {
+  typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  const f2 v = {x, y};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf2));
+}
+
+// A buffer of `bytes` from base (just below 2 GiB of it at most).  The range ends
+// with the last element's 4-byte word, in memory and not from the base, which may
+// lie at any 2 bytes.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_words(const void* base, int64_t bytes) {
+  bytes = (int64_t)((((uintptr_t)base + (uintptr_t)bytes + 3) & ~(uintptr_t)3) - (uintptr_t)base);
+  const int32_t n = bytes > 0x7ffffffcLL ? 0x7ffffffc : (int32_t)bytes;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, n, 0x00020000);
+}
+
 // Division by a divisor d fixed for a launch (1 <= d < 2^31) of dividends
 // n in [0, 2^31), as a multiply and a shift: with l = ceil(log2 d), s = 31 + l
 // and m = ceil(2^s / d) (< 2^32), n / d = floor(n m / 2^s).  (m d - 2^s lies

@@ -40,14 +40,6 @@ struct SmallGeo {
   FastDiv ti, pt, nh, cpc, rs, ns;
 };
 
-// (the range ends with the last element's 4-byte word, in memory and not from
-// the base, which may lie at any 2 bytes)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_m(const void* base, int64_t bytes) {
-  bytes = (int64_t)((((uintptr_t)base + (uintptr_t)bytes + 3) & ~(uintptr_t)3) - (uintptr_t)base);
-  const int32_t n = bytes > 0x7ffffffcLL ? 0x7ffffffc : (int32_t)bytes;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, n, 0x00020000);
-}
-
 template <typename TI, typename TO, int PB, int KF>
 __global__ __launch_bounds__(1024) void conv_small(const TI* __restrict__ In,
                                                    const TI* __restrict__ Ker,
@@ -77,12 +69,12 @@ __global__ __launch_bounds__(1024) void conv_small(const TI* __restrict__ In,
   const int pl = min(p0 + TP, a.hw) - 1;  // last output
   const int x0 = a.sw * fdiv(p0, t.nh);   // first input row
 
-  const __amdgpu_buffer_rsrc_t kr = rsrc_m(Ker, (int64_t)a.Nk * a.Nc * RS * ES);
+  const __amdgpu_buffer_rsrc_t kr = rsrc_words(Ker, (int64_t)a.Nk * a.Nc * RS * ES);
   const uint32_t krow = (uint32_t)(a.Nc * RS * ES);
   const int kf = min(k0 + l16 % KF, a.Nk - 1);
   const uint32_t kbase = (uint32_t)kf * krow + 16u * g;
   const int64_t in0 = (int64_t)b * a.in_img + (int64_t)x0 * a.Ny;
-  const __amdgpu_buffer_rsrc_t ir = rsrc_m(In + in0, (a.in_total - in0) * ES);
+  const __amdgpu_buffer_rsrc_t ir = rsrc_words(In + in0, (a.in_total - in0) * ES);
   // the tensors' last bf16 elements, which the range check drops with a dword
   // that straddles the tensor's end
   uint32_t ker_last = 0u, in_last = 0u;

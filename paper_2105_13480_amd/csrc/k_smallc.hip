@@ -47,13 +47,6 @@ struct SmallcDiv {
   int Smax;    // slab rows LDS holds
 };
 
-__device__ __forceinline__ uint32_t pk2_bf16(float x, float y) {
-  typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  const f2 v = {x, y};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf2));
-}
-
 // KS: largest number of K-steps (ceil(Nc*Nr/2)) the registers hold.  SH2:
 // sh == 2 (operands gathered with 32-bit LDS reads).  FC, FR, FS, FST: a
 // fixed stencil (Nc, Nr, Ns and both strides) compiled in, 0 for any: the
@@ -321,7 +314,7 @@ __global__ __launch_bounds__(256, 2) void conv_smallc(const bf16_t* __restrict__
 #pragma unroll
           for (int j = 0; j < 16; j += 2)
             xp[(4 * (j >> 2) + 2 * half + ((j & 3) >> 1)) * NB * 32 + nb * 32 + l32] =
-                pk2_bf16(acc[mb][nb][j], acc[mb][nb][j + 1]);
+                pk_bf16(acc[mb][nb][j], acc[mb][nb][j + 1]);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // wave-private
 #pragma unroll
         for (int it = 0; it < 16 / RPI; ++it) {

@@ -77,14 +77,6 @@ struct TileGeo {
   FastDiv ipr, ctd;       // work items per row and columns of a band
 };
 
-// (the range ends with the last element's 4-byte word, in memory and not from
-// the base, which may lie at any 2 bytes)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_t(const void* base, int64_t bytes) {
-  bytes = (int64_t)((((uintptr_t)base + (uintptr_t)bytes + 3) & ~(uintptr_t)3) - (uintptr_t)base);
-  const int32_t n = bytes > 0x7ffffffcLL ? 0x7ffffffc : (int32_t)bytes;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, n, 0x00020000);
-}
-
 __device__ __forceinline__ f32x16_t mfma_t(const u32x4_t& a, const u32x4_t& b, const f32x16_t& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                  __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
@@ -120,12 +112,6 @@ __device__ __forceinline__ void static_for(F&& f) {
 // Two fp32 values as three pairs of bf16 that sum to them exactly: the top
 // 8 bits (truncated, so that the largest values do not round to infinity),
 // then the rest rounded to nearest, then what that rounding left.
-__device__ __forceinline__ uint32_t pk_bf16(float x, float y) {
-  typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  const f2 v = {x, y};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf2));
-}
 struct Split3 {
   uint32_t p[3];
 };
@@ -238,7 +224,7 @@ __global__ __launch_bounds__(64 * WM * WN, (tile_occ<TI, WM * WN, OCC, FORM>() *
   // ---- In work items
   const int grp0 = WPG > 1 ? wave / WPG : wave * GPW;  // first channel group of the wave
   const int pt0 = WPG > 1 ? (wave % WPG) * 64 + lane : lane;
-  const __amdgpu_buffer_rsrc_t ir = rsrc_t(In + (int64_t)b0 * a.in_img,
+  const __amdgpu_buffer_rsrc_t ir = rsrc_words(In + (int64_t)b0 * a.in_img,
                                            (a.in_total - (int64_t)b0 * a.in_img) * ES);
   // Lanes write 8 consecutive vectors each, 128 bytes apart: half of them
   // write the columns of each pair in the other order, which spreads the
@@ -286,7 +272,7 @@ __global__ __launch_bounds__(64 * WM * WN, (tile_occ<TI, WM * WN, OCC, FORM>() *
   // 36 contiguous bytes.  1x1: 16 bytes of channels.  Runtime stencils: a run
   // of TPI taps (the last run of a longer stencil ends with its last tap).
   const int64_t ker_total = (int64_t)a.Nk * a.Nc * RS;
-  const __amdgpu_buffer_rsrc_t kr = rsrc_t(Ker, ker_total * ES);
+  const __amdgpu_buffer_rsrc_t kr = rsrc_words(Ker, ker_total * ES);
   constexpr int CPI = K1 ? EPC : F32 ? 1 : 2;
   constexpr int TPI = 16 / ES;
   constexpr int CI = TC / CPI;  // channel items of a stage
@@ -797,7 +783,7 @@ __global__ __launch_bounds__(64 * WM * WN, (tile_occ<TI, WM * WN, OCC, FORM>() *
   constexpr int NROW = O16 ? 16 : 32;        // features (pairs) of a block row
   uint32_t* xp = reinterpret_cast<uint32_t*>(smem) + wave * NROW * NB * 32;
   const __amdgpu_buffer_rsrc_t orr =
-      rsrc_t(Out + (int64_t)b0 * a.Nk * a.hw,
+      rsrc_words(Out + (int64_t)b0 * a.Nk * a.hw,
              (a.out_total - (int64_t)b0 * a.Nk * a.hw) * (int64_t)sizeof(TO));
   const int ch = lane % CPR, frow = lane / CPR;
   // byte offsets of the chunk's outputs, feature k0; past every feature's end
