@@ -92,8 +92,7 @@ typedef enum cnn_kernel {
                          outputs (variants from 3300 on: 16 or 8 features x tp
                          outputs of one image, the contraction shared by the
                          workgroup's waves, a fixed order; tc of its plans is Nc,
-                         or the channels of a chunk where the budget's LDS asks
-                         for fewer; 0 to cnn_plan_tiles)                          */
+                         0 to cnn_plan_tiles)                                     */
   CNN_K_POINTWISE = 3,/* 1x1 stencils, any stride, bf16, Nc % 8 == 0: the inputs of the
                          tile's outputs gathered (no halo, no unused rows), 64 channels
                          per stage, raw Ker rows as in CNN_K_IGEMM_RAWK              */
@@ -162,7 +161,9 @@ typedef enum cnn_kernel {
                          either: a workgroup takes every channel and writes Out
                          in a fixed order.  They are plans of the few-outputs
                          kernel of CNN_K_IGEMM: asked for as tk 32, tp 64 and tc
-                         128, their tk, tp, tc, grid and LDS are its launch's  */
+                         128, their tk, tp, grid and LDS are its launch's, tc Nc
+                         or the channels of a chunk where the budget's LDS asks
+                         for fewer                                             */
   CNN_K_AUTO_NO_WORKSPACE = 14 /* (cnn_plan_tiles only) the model's choice among the
                          plans that need no workspace: the plan cnn_fwd runs
                          when no cnn_plan_find result is cached              */

@@ -417,7 +417,7 @@ int run_plan(const void* In, const void* Ker, void* Out, const cnn_plan_t& pl, h
     e = launch_igemm2(*v2, In, Ker, Out, ws, a, pl.lds_bytes, st);
   } else if (const VariantM* vm = small_variant(pl)) {
     SmallShape ms;
-    if (!small_plan_ok(*vm, pl, &ms))
+    if (pl.tc != pl.prob.Nc || !small_plan_ok(*vm, pl, &ms))
       return fail(CNN_E_PLAN, "plan names no matching kernel instantiation (variant %d)", pl.variant);
     if (dry) return CNN_OK;
     e = launch_small(*vm, In, Ker, Out, a, ms, st);

@@ -441,7 +441,8 @@ static const VariantT* tile_variant(int kernel, int id) {
 static bool small_plan(const cnn_problem& p, int dtype, int id, const VariantM& v,
                        const SmallShape& s, const cnn_budget& bud, cnn_plan_t* plan) {
   if (!eval_tiling(p, dtype, id, v.tk, v.tp, p.Nc, v.acc, s.S, s.lds, 0, bud, plan)) return false;
-  // (tc: Nc unless the budget asks for smaller chunks than LDS holds)
+  // (tc: Nc unless the budget asks for smaller chunks than LDS holds, which only
+  // the direct channel-slice plans have)
   SmallShape whole;
   if (small_geometry(v, p, dtype, 160 * 1024, 0, &whole) && whole.chk != s.chk) plan->tc = s.chk;
   plan->grid = s.grid;
@@ -457,7 +458,7 @@ static bool eval_small(const cnn_problem& p, int dtype, const VariantM& v, const
   SmallShape s;
   // few outputs: up to four workgroups per CU (with 20 per CU a 3-channel
   // 3x3 stride-2 layer ran 30 us against 19 on the few-channel kernel)
-  return small_geometry(v, p, dtype, bud.lds_bytes, 0, &s) && s.grid <= 4 * bud.cus &&
+  return small_geometry(v, p, dtype, 160 * 1024, 0, &s) && s.grid <= 4 * bud.cus &&
          small_plan(p, dtype, v.id, v, s, bud, plan);
 }
 

@@ -443,11 +443,18 @@ def test_direct_slice_plans_describe_their_launch(dtype):
         for lds in (160 * 1024, 130 * 1024):
             bud = cnn.budget(lds_bytes=lds)
             pl = cnn.plan_tiles(p, dtype, cnn.K_SPLITC, 32, 64, 128, bud)
-            own = cnn.plan_tiles(p, dtype, cnn.K_IGEMM, pl.tk, pl.tp, 0, bud)
-            assert pl.variant == 2509 + dtype and 3300 <= own.variant < 3400
-            for f in ("tk", "tp", "tc", "grid", "lds_bytes", "slab_rows", "ws_bytes", "mfma_flops"):
+            assert pl.variant == 2509 + dtype and pl.lds_bytes <= lds
+            own = cnn.plan_tiles(p, dtype, cnn.K_IGEMM, pl.tk, pl.tp, 0, cnn.budget())
+            assert 3300 <= own.variant < 3400
+            same = ["tk", "tp", "grid", "slab_rows", "ws_bytes", "mfma_flops"]
+            if own.lds_bytes <= lds:
+                same += ["tc", "lds_bytes"]
+            else:  # in smaller chunks
+                assert pl.tc < dims[1] and pl.tc % 32 == 0
+                with pytest.raises(cnn.CnnError):
+                    cnn.plan_tiles(p, dtype, cnn.K_IGEMM, pl.tk, pl.tp, 0, bud)
+            for f in same:
                 assert getattr(pl, f) == getattr(own, f), f
-            assert pl.lds_bytes <= lds
             assert cnn.hbm_bytes(pl) == cnn.hbm_bytes(own)
             assert (pl.variant, pl.tp) in {(c.variant, c.tp) for c in cnn.plan_candidates(p, dtype, bud)}
             for change in ({"kc": 2}, {"tp": 48}, {"grid": pl.grid + 1}, {"tc": 96 if pl.tc != 96 else 64},
@@ -458,6 +465,12 @@ def test_direct_slice_plans_describe_their_launch(dtype):
                 st = L.cnn_fwd_plan_ws(0x1000, 0x40000000, 0x80000000, ctypes.byref(p), dtype,
                                        ctypes.byref(q), None, 0, None)
                 assert st == -8, change
+    # chunks of channels are the direct plans' alone
+    p = cnn.problem(1, 1024, 512, 7, 7, 3, 3, 1, 1)
+    own = cnn.plan_tiles(p, dtype, cnn.K_IGEMM, 16, 16, 0, cnn.budget())
+    own.tc = 512
+    assert L.cnn_fwd_plan_ws(0x1000, 0x40000000, 0x80000000, ctypes.byref(p), dtype,
+                             ctypes.byref(own), None, 0, None) == -8
     # beyond that kernel's 32-bit offsets the request is still accepted
     far = cnn.plan_tiles(cnn.problem(1, 1 << 25, 32, 1, 1, 3, 3, 1, 1), dtype, cnn.K_SPLITC, 32, 64,
                          128, cnn.budget())
